@@ -488,6 +488,7 @@ vlbm_status vlbm_create(const vlbm_params* p, vlbm_ctx** out) {
   c->L.dim = c->D;
   c->L.model = p->model;
   c->L.block_x = p->block_x ? p->block_x : (p->nx >= 256 ? 256 : (p->nx >= 128 ? 128 : 64));
+  c->L.block_flat = p->block_x ? p->block_x : (c->N < 256 * 256 ? 64 : 256);
   c->L.stream = c->stream;
   *out = c;
   return VLBM_OK;

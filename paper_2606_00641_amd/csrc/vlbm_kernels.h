@@ -73,7 +73,8 @@ struct Codec {
 
 struct Launch {
   int storage, dim, model;
-  int block_x;
+  int block_x;     // workgroup width where the workgroups tile the x rows
+  int block_flat;  // where they do not and take consecutive cells of the lattice
   hipStream_t stream;
 };
 
