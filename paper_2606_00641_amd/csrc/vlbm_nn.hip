@@ -75,7 +75,6 @@ __device__ __forceinline__ bf16_t f2bf(float f) {
   const unsigned u = __float_as_uint(f);
   return (bf16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);  // nearest even (finite)
 }
-__device__ __forceinline__ float bf2f(bf16_t b) { return __uint_as_float((unsigned)b << 16); }
 
 // exact GELU and its derivative (standard normal CDF via erf)
 __device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
@@ -84,6 +83,58 @@ __device__ __forceinline__ float gelu_grad(float z) {
   const float pdf = 0.39894228040143268f * expf(-0.5f * z * z);
   return cdf + z * pdf;
 }
+
+// Asynchronous copy of 16 bytes per lane from global memory to LDS (gfx950): lane l's piece
+// lands at dst + 16 l, dst the same in every lane of the wavefront; inactive lanes copy
+// nothing.  lds_arrived() waits for the wavefront's own copies, the barrier after it for
+// everyone's.
+__device__ __forceinline__ void lds_fetch(const void* src, void* dst) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) unsigned*)src,
+                                   (__attribute__((address_space(3))) unsigned*)dst, 16, 0, 0);
+}
+__device__ __forceinline__ void lds_arrived() { __builtin_amdgcn_s_waitcnt(0x0f70); }  // vmcnt(0)
+
+// Copy of the 18 x 18 halo of the 16 x 16 tile at (ty0, tx0) of slice `in` ([H][W][CIN],
+// periodic) into LDS, channels-last, by NTH threads: piece e = 16 bytes at position e / CH,
+// chunk e % CH.  Away from the slice's edges a piece's address is the tile's plus an offset
+// that is the same for every tile (rel[], set up once: the index arithmetic of a copy was a
+// third of the kernels' vector instructions); at an edge the indices wrap.
+template <int CIN, int NTH>
+struct HaloFetch {
+  static constexpr int CH = CIN / 8, Q = HALO * HALO * CH, N = (Q + NTH - 1) / NTH;
+  unsigned rel[N];  // byte offset of piece j from the halo's first position
+  __device__ __forceinline__ void setup(int W) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const int e = threadIdx.x + j * NTH, pix = e / CH;
+      rel[j] = (unsigned)(((pix / HALO) * W + pix % HALO) * CIN + (e % CH) * 8) * (unsigned)sizeof(bf16_t);
+    }
+  }
+  __device__ __forceinline__ void operator()(const bf16_t* in, int ty0, int tx0, int H, int W, unsigned char* buf) const {
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (ty0 > 0 && tx0 > 0 && ty0 + TILE < H && tx0 + TILE < W) {
+      const char* base = reinterpret_cast<const char*>(in + ((size_t)(ty0 - 1) * W + tx0 - 1) * CIN);
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if ((j + 1) * NTH <= Q || (int)threadIdx.x + j * NTH < Q)
+          lds_fetch(base + rel[j], buf + (64 * wave + j * NTH) * 16);
+      return;
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      int e = threadIdx.x + j * NTH;
+      asm volatile("" : "+v"(e));  // the edge's indices stay here, out of the loop over tiles
+      if (e < Q) {
+        const int pix = e / CH;
+        int gy = ty0 - 1 + pix / HALO;
+        int gx = tx0 - 1 + pix % HALO;
+        gy = gy < 0 ? gy + H : (gy >= H ? gy - H : gy);
+        gx = gx < 0 ? gx + W : (gx >= W ? gx - W : gx);
+        lds_fetch(in + ((size_t)gy * W + gx) * CIN + (e % CH) * 8, buf + (64 * wave + j * NTH) * 16);
+      }
+    }
+  }
+};
 
 // ---------------------------------------------------------------------------
 // weight packing into B-fragment order
@@ -289,108 +340,221 @@ __global__ __launch_bounds__(kConvThreads) void k_conv(const bf16_t* __restrict_
 // D-slice lattices (as k_conv); blockIdx.y selects the z-slab of a 3x3x3 kernel
 // (gridDim.y = 3; taps 9 kz + 3 ky + kx, columns of the partial tap * CIN + c over
 // all 27 taps) or is 0 for the 3x3 kernel (gridDim.y = 1).
+//
+// Both operands need consecutive positions of one channel per lane, while the tiles are
+// channels-last: they are copied to LDS as they are and read with ds_read_b64_tr_b16,
+// which hands lane i of 16 the four positions of channel i that its group addresses (lane
+// 4 r + q: position r, channels 4 q..4 q + 3).  One such read is half an operand: the 16
+// positions of one tile row, lane group g the positions 4 g..4 g + 3, and an operand is
+// two consecutive rows.  A wavefront keeps the rows it has read, so that a halo row serves
+// the three dy it belongs to: 10 reads feed 18 products.  A wavefront takes 16 channels (of
+// 32: a column tile per dx) or, for 8 input channels, a column tile of two dx, and a quarter
+// of the tile's rows; eight wavefronts, so that a workgroup loads the four SIMDs evenly and
+// two fit a CU (with six, the second did not: 144 us against 87).  The next tile's halo and
+// dZ are copied to the other half of the LDS during the products.
+// Bound by the tiles' traffic (halo and dZ, 380 MB for 32 x 32 channels on 40 x 256^2
+// positions): 87 us, 4.4 TB/s.  Reading the operands from a channel-major copy, one 16-bit
+// element at a time, and summing db from LDS took 307 us.
 // ---------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+
 template <int CIN, int COUT>
-__global__ __launch_bounds__(kThreads) void k_conv_bw(const bf16_t* __restrict__ act, const bf16_t* __restrict__ dz,
-                                                      int S, int D, int H, int W, float* __restrict__ part_w,
-                                                      float* __restrict__ part_b) {
+struct BwShape {
+  static constexpr int NC = 2;                  // column groups: 16 channels, or pairs of dx
+  static constexpr int CT = CIN == 32 ? 3 : 1;  // 16-column tiles (dx) per group and dy
+  static constexpr int KS = 4;                  // shares of the tile's rows
+  static constexpr int NW = NC * KS, NTH = 64 * NW;
+  static constexpr int MT = (COUT + 15) / 16;
+};
+
+// elements at byte offset `off` of an LDS array, transposed over 16 lanes
+__device__ __forceinline__ s16x4 lds_tr(const bf16_t* base, int off) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (__attribute__((address_space(3))) s16x4*)(reinterpret_cast<const char*>(base) + off));
+}
+__device__ __forceinline__ bf16x8 two_rows(s16x4 a, s16x4 b) {
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+template <int CIN, int COUT>
+__global__ __launch_bounds__((BwShape<CIN, COUT>::NTH), 4) void k_conv_bw(const bf16_t* __restrict__ act,
+                                                                     const bf16_t* __restrict__ dz, int S, int D,
+                                                                     int H, int W, float* __restrict__ part_w,
+                                                                     float* __restrict__ part_b) {
+  using B = BwShape<CIN, COUT>;
+  constexpr int NC = B::NC, CT = B::CT, KS = B::KS, NTH = B::NTH, MT = B::MT;
   constexpr int NJ = 9 * CIN;  // columns of this z-slab
-  constexpr int NTJ = (NJ + 15) / 16;
-  constexpr int MT = (COUT + 15) / 16;
-  constexpr int NTW = (NTJ + 3) / 4;  // N tiles per wavefront
-  // LDS rows padded against bank conflicts: a channel's halo (324 elements) to 326, an
-  // odd number of dwords, so that the 16 channels a lane group reads fall in distinct
-  // banks; a row of dZ (256 positions, 512 bytes: every lane of a group in one bank) by
-  // 8 elements, 33 16-byte groups.
-  constexpr int AS = HALO * HALO + 2;
-  constexpr int DZS = TILE * TILE + 8;
-  __shared__ __attribute__((aligned(16))) bf16_t aT[CIN * AS];
-  __shared__ __attribute__((aligned(16))) bf16_t dzT[MT * 16 * DZS];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 4;
-  f32x4 acc[MT][NTW];
+  constexpr int OH = COUT / 8, QD = TILE * TILE * OH, ND = (QD + NTH - 1) / NTH;  // 16-byte pieces of dZ
+  static_assert(NTH % OH == 0, "a thread's pieces of dZ hold the same channels");
+  // two tiles; after them the accumulators of the other row shares, then the db sums.  The
+  // 32 elements past each tile are read by lanes whose column (dx = 3) or row (o >= COUT)
+  // is dropped.
+  constexpr int kA = HALO * HALO * CIN + 32, kD = TILE * TILE * COUT + 32;
+  constexpr int kAcc = CT * 3 * MT * 4;  // accumulator registers per lane
+  constexpr int kTiles = (kA + kD) * 2, kSum = NC * kAcc * 64 * 4, kDb = NTH * 8 * 4;
+  constexpr int kMax = kSum > kDb ? kSum : kDb;
+  // two arrays, not one: reads of one then need not wait for copies into the other
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kTiles > kMax ? kTiles : kMax];
+  __shared__ __attribute__((aligned(16))) unsigned char lds2[kTiles];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 4, r = (lane & 15) >> 2, q = lane & 3;
+  const int col = wv % NC, ks = wv / NC;
+  f32x4 acc[3][CT][MT];
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+  for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
-    for (int u = 0; u < NTW; ++u) acc[mt][u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  float db = 0.0f;
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) acc[dy][ct][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  float db[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
   const int slab = blockIdx.y, nslab = gridDim.y;
   const int tiles_x = W / TILE, tiles_y = H / TILE;
   const int ntile = S * tiles_x * tiles_y;
-  for (int tid = blockIdx.x; tid < ntile; tid += gridDim.x) {
+  HaloFetch<CIN, NTH> halo;
+  halo.setup(W);
+  unsigned drel[ND];  // byte offset of the thread's pieces of dZ in their tile
+#pragma unroll
+  for (int j = 0; j < ND; ++j) {
+    const int e = threadIdx.x + j * NTH, p = e / OH;
+    drel[j] = (unsigned)(((p / TILE) * W + p % TILE) * COUT + (e % OH) * 8) * (unsigned)sizeof(bf16_t);
+  }
+  const int swv = __builtin_amdgcn_readfirstlane(wv);
+  auto fetch = [&](int tid, unsigned char* buf) {
     const int sl = tid / (tiles_x * tiles_y);
     const int rem = tid % (tiles_x * tiles_y);
     const int ty0 = (rem / tiles_x) * TILE, tx0 = (rem % tiles_x) * TILE;
     const int zl = sl % D;
     int gz = zl + slab - nslab / 2;
     gz = gz < 0 ? gz + D : (gz >= D ? gz - D : gz);
-    const int asl = sl - zl + gz;  // input slice of this z-slab
-    __syncthreads();  // previous tile fully consumed
-    for (int q = threadIdx.x; q < HALO * HALO * (CIN / 8); q += kThreads) {
-      const int pix = q / (CIN / 8), ch = q % (CIN / 8);
-      const int hy = pix / HALO, hx = pix % HALO;
-      int gy = ty0 - 1 + hy;
-      int gx = tx0 - 1 + hx;
-      gy = gy < 0 ? gy + H : (gy >= H ? gy - H : gy);
-      gx = gx < 0 ? gx + W : (gx >= W ? gx - W : gx);
-      const uint4 v = *reinterpret_cast<const uint4*>(act + (((size_t)asl * H + gy) * W + gx) * CIN + ch * 8);
-      const bf16_t* e = reinterpret_cast<const bf16_t*>(&v);
+    halo(act + (size_t)(sl - zl + gz) * H * W * CIN, ty0, tx0, H, W, buf);  // this z-slab's input slice
+    const char* dt = reinterpret_cast<const char*>(dz + (((size_t)sl * H + ty0) * W + tx0) * COUT);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) aT[(ch * 8 + j) * AS + hy * HALO + hx] = e[j];
-    }
-    for (int q = threadIdx.x; q < MT * 16 * TILE * TILE; q += kThreads) {
-      const int o = q / (TILE * TILE), p = q % (TILE * TILE);
-      const int y = ty0 + p / TILE, x = tx0 + p % TILE;
-      dzT[o * DZS + p] = o < COUT ? dz[(((size_t)sl * H + y) * W + x) * COUT + o] : (bf16_t)0;
-    }
-    __syncthreads();
-    if (slab == 0 && (int)threadIdx.x < COUT) {
-      float sacc = 0.0f;
-      for (int p = 0; p < TILE * TILE; ++p) sacc += bf2f(dzT[threadIdx.x * DZS + p]);
-      db += sacc;
-    }
+    for (int j = 0; j < ND; ++j)
+      if ((j + 1) * NTH <= QD || (int)threadIdx.x + j * NTH < QD)
+        lds_fetch(dt + drel[j], buf + kA * 2 + (64 * swv + j * NTH) * 16);
+  };
+  auto products = [&](const unsigned char* buf) {
+    const bf16_t* aS = reinterpret_cast<const bf16_t*>(buf);
+    const bf16_t* dS = aS + kA;
+    if (slab == 0) {
 #pragma unroll
-    for (int s = 0; s < (TILE * TILE) / 32; ++s) {
-      bf16x8 afr[MT];
+      for (int j = 0; j < ND; ++j) {
+        const int e = threadIdx.x + j * NTH;
+        if (e < QD) {
+          const uint4 v = *reinterpret_cast<const uint4*>(dS + e * 8);
+          const unsigned w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int h = 0; h < 4; ++h) {
+            db[2 * h] += __uint_as_float(w[h] << 16);
+            db[2 * h + 1] += __uint_as_float(w[h] & 0xffff0000u);
+          }
+        }
+      }
+    }
+    const int r0 = ks * (TILE / KS);
+    // bytes of this lane's element of halo row 0 (of the column group) and of dZ row 0
+    const int ab = (4 * g + r) * CIN * 2 + 8 * q + 32 * col;
+    const int zb = (4 * g + r) * COUT * 2 + 8 * q;
+    s16x4 b[4][CT];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) b[h][ct] = lds_tr(aS, ab + ((r0 + h) * HALO + ct) * CIN * 2);
+#pragma unroll
+    for (int st = 0; st < TILE / KS / 2; ++st) {
+      const int row = r0 + 2 * st;
+#pragma unroll
+      for (int h = 2; h < 4; ++h)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) b[h][ct] = lds_tr(aS, ab + ((row + h) * HALO + ct) * CIN * 2);
+      bf16x8 a[MT];
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
-        afr[mt] = *reinterpret_cast<const bf16x8*>(dzT + (16 * mt + (lane & 15)) * DZS + 32 * s + 8 * g);
-      const int pos0 = 32 * s + 8 * g;  // 8 consecutive positions of one tile row
-      const int py = pos0 / TILE, px0 = pos0 % TILE;
+        a[mt] = two_rows(lds_tr(dS, zb + row * TILE * COUT * 2 + 32 * mt),
+                         lds_tr(dS, zb + (row + 1) * TILE * COUT * 2 + 32 * mt));
 #pragma unroll
-      for (int u = 0; u < NTW; ++u) {
-        const int nt = wv + 4 * u;
-        if (nt >= NTJ) continue;
-        const int j = 16 * nt + (lane & 15);
-        bf16x8 bfr = bf16x8{};
-        if (j < NJ) {
-          const int tap = j / CIN, c = j % CIN;
-          const int dy = tap / 3, dx = tap % 3;
-          const bf16_t* src = aT + c * AS + (py + dy) * HALO + px0 + dx;  // 8 positions, unaligned
+      for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
-          for (int e = 0; e < 8; ++e) bfr[e] = __builtin_bit_cast(__bf16, src[e]);
+        for (int ct = 0; ct < CT; ++ct) {
+          const bf16x8 bb = two_rows(b[dy][ct], b[dy + 1][ct]);
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+            acc[dy][ct][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt], bb, acc[dy][ct][mt], 0, 0, 0);
         }
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          acc[mt][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr[mt], bfr, acc[mt][u], 0, 0, 0);
+      for (int ct = 0; ct < CT; ++ct) {
+        b[0][ct] = b[2][ct];
+        b[1][ct] = b[3][ct];
       }
     }
+  };
+  int tid = blockIdx.x;
+  const int step = gridDim.x;
+  if (tid < ntile) fetch(tid, lds);
+  for (; tid < ntile; tid += 2 * step) {
+    lds_arrived();
+    __syncthreads();  // this tile is here; the previous one is fully consumed
+    if (tid + step < ntile) fetch(tid + step, lds2);
+    products(lds);
+    if (tid + step >= ntile) break;
+    lds_arrived();
+    __syncthreads();
+    if (tid + 2 * step < ntile) fetch(tid + 2 * step, lds);
+    products(lds2);
   }
-  // partial results of this workgroup
+  // the row shares of a column group are added in order, then written as this workgroup's
+  // partial
+  float* sum = reinterpret_cast<float*>(lds);
+  for (int h = 1; h < KS; ++h) {
+    __syncthreads();
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+    for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
-    for (int u = 0; u < NTW; ++u) {
-      const int nt = wv + 4 * u;
-      if (nt >= NTJ) continue;
-      const int j = 16 * nt + (lane & 15);
+      for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int o = 16 * mt + 4 * g + r;
-        if (o < COUT && j < NJ)
-          part_w[((size_t)blockIdx.x * COUT + o) * (nslab * NJ) + slab * NJ + j] = acc[mt][u][r];
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (ks == h) sum[(col * kAcc + ((dy * CT + ct) * MT + mt) * 4 + e) * 64 + lane] = acc[dy][ct][mt][e];
+    __syncthreads();
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (ks == 0) acc[dy][ct][mt][e] += sum[(col * kAcc + ((dy * CT + ct) * MT + mt) * 4 + e) * 64 + lane];
+  }
+  if (ks == 0) {
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const int dx = CIN == 32 ? ct : 2 * col + ((lane & 15) >> 3);
+        const int c = CIN == 32 ? 16 * col + (lane & 15) : (lane & 7);
+        const int j = (3 * dy + dx) * CIN + c;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int o = 16 * mt + 4 * g + e;
+            if (o < COUT && dx < 3)
+              part_w[((size_t)blockIdx.x * COUT + o) * (nslab * NJ) + slab * NJ + j] = acc[dy][ct][mt][e];
+          }
       }
-    }
-  if (slab == 0 && (int)threadIdx.x < COUT) part_b[(size_t)blockIdx.x * COUT + threadIdx.x] = db;
+  }
+  if (slab != 0) return;  // the same in every thread
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 8; ++h) sum[threadIdx.x * 8 + h] = db[h];
+  __syncthreads();
+  if ((int)threadIdx.x < COUT) {
+    const int ch = threadIdx.x / 8, h = threadIdx.x % 8;
+    float v = 0.0f;
+    for (int t = ch; t < NTH; t += OH) v += sum[t * 8 + h];
+    part_b[(size_t)blockIdx.x * COUT + threadIdx.x] = v;
+  }
 }
 
 // Sum the workgroups' partials into the master-layout gradient:
@@ -870,18 +1034,19 @@ hipError_t launch_conv(int cin, int cout, int mode, int nzt, const bf16_t* act, 
 
 hipError_t launch_conv_bw(int cin, int cout, int nzt, const bf16_t* act, const bf16_t* dz, int S, int D, int H,
                           int W, float* part_w, float* part_b, int nblk, hipStream_t s) {
-  const dim3 grd(nblk, nzt), blk(kThreads);
-  if (cin == 8 && cout == 32)
-    hipLaunchKernelGGL((k_conv_bw<8, 32>), grd, blk, 0, s, act, dz, S, D, H, W, part_w, part_b);
-  else if (cin == 32 && cout == 32)
-    hipLaunchKernelGGL((k_conv_bw<32, 32>), grd, blk, 0, s, act, dz, S, D, H, W, part_w, part_b);
-  else if (cin == 32 && cout == 8)
-    hipLaunchKernelGGL((k_conv_bw<32, 8>), grd, blk, 0, s, act, dz, S, D, H, W, part_w, part_b);
-  else if (cin == 8 && cout == 8)
-    hipLaunchKernelGGL((k_conv_bw<8, 8>), grd, blk, 0, s, act, dz, S, D, H, W, part_w, part_b);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+  const dim3 grd(nblk, nzt);
+#define BW_CASE(CI, CO)                                                                                     \
+  if (cin == CI && cout == CO) {                                                                            \
+    hipLaunchKernelGGL((k_conv_bw<CI, CO>), grd, dim3(BwShape<CI, CO>::NTH), 0, s, act, dz, S, D, H, W,     \
+                       part_w, part_b);                                                                     \
+    return hipGetLastError();                                                                               \
+  }
+  BW_CASE(8, 32)
+  BW_CASE(32, 32)
+  BW_CASE(32, 8)
+  BW_CASE(8, 8)
+#undef BW_CASE
+  return hipErrorInvalidValue;
 }
 
 vlbm_status repack(vlbm_nn* nn) {
@@ -1201,7 +1366,8 @@ vlbm_status vlbm_nn_loss_grad(vlbm_nn* nn, const float* X, const float* T, int32
   // backward: dZ of layer l lives in d_dz[cur]
   int cur = 0;
   const int ntile = S * (nx / TILE) * (ny / TILE);
-  const int nblk = ntile < nn->bw_blocks ? ntile : nn->bw_blocks;
+  // about two workgroups per CU over all z-slabs (the partials' traffic grows with them)
+  const int most = nn->bw_blocks / nn->nzt, nblk = ntile < most ? ntile : most;
   for (int l = L - 1; l >= 0; --l) {
     NN_HIP(nn, launch_conv_bw(nn->ci[l], nn->co[l], nn->nzt, nn->d_act[l], nn->d_dz[cur], S, nz, ny, nx,
                               nn->d_part_w, nn->d_part_b, nblk, nn->stream));
