@@ -951,7 +951,9 @@ void launch_k(const Launch& L, dim3 grd, int parity, int coll, bool xch, bool fx
   auto go = [&](auto par_c, auto coll_c, auto xch_c, auto fx_c) {
     constexpr int P = decltype(par_c)::value, C = decltype(coll_c)::value;
     constexpr bool X = decltype(xch_c)::value, FXv = decltype(fx_c)::value;
-    if constexpr (BODY == 0 && !FXv) {
+    // (the injecting sweep in 16-bit storage keeps its row workgroups: the compiler contracts
+    // the flat form differently, which moves the BF16 rounding of single populations)
+    if constexpr (BODY == 0 && !FXv && !(INJ && (ST == ST_F16 || ST == ST_BF16))) {
       if (flat_rows(L, g)) {
         hipLaunchKernelGGL((k_sweep<ST, D, MODEL, P, BODY, C, INJ, P == 1 && MODEL != 1, false, 0, true>),
                            flat_grid(L, g, 1), dim3(L.block_flat), 0, L.stream, g, ph, cd, b, dq, flag, in, mo);
