@@ -3,12 +3,12 @@
 // FP64 gate and the corrected coarse step.
 //
 // Convolutions are implicit GEMMs on v_mfma_f32_16x16x32_bf16 (gfx950): one
-// workgroup (8 wavefronts, two tile rows each) computes a 16 x 16 tile of output positions for every
+// workgroup (8 wavefronts) computes 16 x 16 tiles of output positions for every
 // output channel; the 18 x 18 input halo (periodic) is staged in LDS in
-// channels-last order so that one lane's A fragment (8 consecutive input channels
+// channels-last order so that one lane's operand (8 consecutive input channels
 // of one tap, or 8 taps' worth for 8-channel inputs) is a single 16-byte LDS read.
-// B fragments (weights) are packed once per weight update in the exact lane order
-// of the instruction and held in registers for the whole tile.
+// The weights are packed once per weight update in the exact lane order of the
+// instruction and held in registers.
 //
 // MFMA 16x16x32 operand layout (verified on the device): lane l holds
 // A[i = l % 16][k = 8 (l / 16) + e] and B[k = 8 (l / 16) + e][j = l % 16] for
@@ -39,11 +39,7 @@ typedef unsigned short bf16_t;
 constexpr int TILE = 16;
 constexpr int HALO = TILE + 2;
 constexpr int kThreads = 256;
-// Convolution workgroups: eight wavefronts, two tile rows each (measured against four
-// rows per wavefront: 13 % faster on a 256^2 lattice, 10 % on 384 x 192 x 192 in 3D;
-// one row per wavefront was slower again).
-constexpr int kConvRows = 2;
-constexpr int kConvThreads = 64 * (TILE / kConvRows);
+constexpr int kConvThreads = 512;  // eight wavefronts
 constexpr int kMaxLayers = 8;
 constexpr int kGateThreads = 256;
 
@@ -76,12 +72,79 @@ __device__ __forceinline__ bf16_t f2bf(float f) {
   return (bf16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);  // nearest even (finite)
 }
 
-// exact GELU and its derivative (standard normal CDF via erf)
-__device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
+// The exact GELU z Phi(z) and its derivative Phi(z) + z phi(z), Phi the standard normal CDF,
+// by Phi(-|z|) = 2^P(|z|) with P a polynomial fitted to log2 Phi(-a) so that the largest
+// error of Phi is least, falling monotonically beyond the fitted range: about a third of
+// the instructions erff takes, which bound the convolutions' epilogues.  The derivative's
+// P has degree 10, fitted on [0, 6] to 1.8e-10: against FP64 on [-8, 8] it is 1.3e-7 off at
+// most, rms 2.4e-8 (by erff and expf 1.4e-7, 2.6e-8).
 __device__ __forceinline__ float gelu_grad(float z) {
-  const float cdf = 0.5f * (1.0f + erff(z * 0.70710678118654752f));
-  const float pdf = 0.39894228040143268f * expf(-0.5f * z * z);
-  return cdf + z * pdf;
+  const float a = fabsf(z);
+  float p = -5.180444873e-08f;
+  p = fmaf(p, a, 1.324517939e-06f);
+  p = fmaf(p, a, -1.481894560e-05f);
+  p = fmaf(p, a, 9.329344903e-05f);
+  p = fmaf(p, a, -3.217124904e-04f);
+  p = fmaf(p, a, 6.053244942e-05f);
+  p = fmaf(p, a, 6.898670457e-03f);
+  p = fmaf(p, a, -5.242214724e-02f);
+  p = fmaf(p, a, -4.592237473e-01f);
+  p = fmaf(p, a, -1.151104093e+00f);
+  p = fmaf(p, a, -1.0f);
+  const float h = __builtin_amdgcn_exp2f(p), cdf = z < 0.0f ? h : 1.0f - h;
+  return fmaf(z, 0.39894228040143268f * __builtin_amdgcn_exp2f(z * z * -0.72134752044448170f), cdf);
+}
+
+// two floats as BF16, nearest even (one instruction), a in the low half
+__device__ __forceinline__ unsigned bf16_pair(float a, float b) {
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+  bf16x2 v;
+  v[0] = (__bf16)a;
+  v[1] = (__bf16)b;
+  return __builtin_bit_cast(unsigned, v);
+}
+
+// Four GELU values as BF16: max(z, 0) - |z| Phi(-|z|), P of degree 8 fitted on [0, 5.5] to
+// 7.6e-9.  The activations are those of GELU by erff, bit for bit (but for the sign of
+// zero): over all finite z the value here differs from erff's by less than 1.77e-7 |z|
+// (compared for every float), so where +-1.8e-7 |z| rounds to one BF16 value that is the
+// one; the rest (7 in 10^4 values of a standard normal z) take erff, one value per lane and
+// turn.
+__device__ __forceinline__ uint2 gelu_bf16(const float4 z) {
+  const float zz[4] = {z.x, z.y, z.z, z.w};
+  float lo[4], hi[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float a = fabsf(zz[i]);
+    float p = -2.766420039e-06f;
+    p = fmaf(p, a, 3.856343756e-05f);
+    p = fmaf(p, a, -1.823183993e-04f);
+    p = fmaf(p, a, -1.463305234e-04f);
+    p = fmaf(p, a, 7.075964473e-03f);
+    p = fmaf(p, a, -5.250530317e-02f);
+    p = fmaf(p, a, -4.592048228e-01f);
+    p = fmaf(p, a, -1.151105762e+00f);
+    p = fmaf(p, a, -1.0f);
+    const float v = fmaf(-a, __builtin_amdgcn_exp2f(p), fmaxf(zz[i], 0.0f));
+    lo[i] = fmaf(a, -1.8e-7f, v);
+    hi[i] = fmaf(a, 1.8e-7f, v);
+  }
+  uint2 v = make_uint2(bf16_pair(lo[0], lo[1]), bf16_pair(lo[2], lo[3]));
+  const unsigned dx = v.x ^ bf16_pair(hi[0], hi[1]), dy = v.y ^ bf16_pair(hi[2], hi[3]);
+  if (dx | dy) {
+    unsigned left = ((dx & 0xffffu) ? 1u : 0u) | ((dx >> 16) ? 2u : 0u) | ((dy & 0xffffu) ? 4u : 0u) | ((dy >> 16) ? 8u : 0u);
+    do {
+      const int i = __ffs(left) - 1;
+      const float w = i == 0 ? zz[0] : (i == 1 ? zz[1] : (i == 2 ? zz[2] : zz[3]));
+      const unsigned e = f2bf(0.5f * w * (1.0f + erff(w * 0.70710678118654752f)));
+      if (i == 0) v.x = (v.x & 0xffff0000u) | e;
+      if (i == 1) v.x = (v.x & 0xffffu) | (e << 16);
+      if (i == 2) v.y = (v.y & 0xffff0000u) | e;
+      if (i == 3) v.y = (v.y & 0xffffu) | (e << 16);
+      left &= left - 1;
+    } while (left);
+  }
+  return v;
 }
 
 // Asynchronous copy of 16 bytes per lane from global memory to LDS (gfx950): lane l's piece
@@ -176,158 +239,227 @@ __global__ void k_pack(const float* __restrict__ W, int CI, int CO, int flip, in
 // ---------------------------------------------------------------------------
 // act: BF16 channels-last [S][H][W][CIN] over S = B * D slices (D = 1: a batch of 2D
 // lattices; D > 1: B 3D lattices of D slices each, periodic in z).  NZT = 1 for the
-// 3x3 kernel, 3 for the 3x3x3 kernel (the halos of slices z-1, z, z+1 are staged
-// and the packed weights of each z-slab are loaded in turn).  Output, by MODE:
+// 3x3 kernel, 3 for the 3x3x3 kernel.  Output, by MODE:
 //  HIDDEN: z = conv + bias; out_act (BF16 NHWC COUT) = GELU(z); out_z (FP32 NHWC, optional) = z
 //  LAST:   out_z (FP32 channel-major [COUT][B][H][W]) = (conv + bias) * oscale + oshift
 //  BWD:    out_act (BF16 NHWC COUT) = conv * GELU'(zprev), zprev FP32 NHWC COUT
+//
+// A workgroup works through 16 x 16 tiles, for 3x3x3 kernels up a column of them in z (its
+// share zn of the slices): every input plane is staged once and adds to the three output
+// planes it touches, whose accumulators stay in registers.  The next plane's halo is copied
+// to the other LDS buffer during the products.  A wavefront holds the weights of 16 output
+// channels (of 32) and every tap in registers for its whole life, and takes 4 tile rows (2
+// with 8 output channels, where all eight wavefronts share them); a fragment of a halo row
+// serves the three dy (and, in 3D, three kz) it belongs to.  The weights are the first
+// operand, so that a lane ends with four consecutive channels of one position and stores
+// them without an exchange.
+// Measured for 32 -> 32 channels, staging each tile (in 3D three halos) and re-reading all
+// weights per tile before: 40 x 256^2 positions, z kept, 220 -> 166 us, 384 x 192 x 192
+// in 3D 1676 -> 964 us (products about 340 us of it, vector instructions 380).  Tiles of 32 rows
+// in 3D took 1240 us, and without taking turns 1047 us.
 template <int CIN, int COUT, int MODE, int NZT>
-__global__ __launch_bounds__(kConvThreads) void k_conv(const bf16_t* __restrict__ act, const bf16_t* __restrict__ wpack,
-                                                   const float* __restrict__ bias, int D, int H, int W,
-                                                   bf16_t* __restrict__ out_act, float* __restrict__ out_z,
-                                                   const float* __restrict__ zprev,
-                                                   const float* __restrict__ oscale,
-                                                   const float* __restrict__ oshift) {
+__global__ __launch_bounds__(kConvThreads, NZT == 1 ? 4 : 2) void k_conv(
+    const bf16_t* __restrict__ act, const bf16_t* __restrict__ wpack, const float* __restrict__ bias, int S, int D,
+    int H, int W, int zn, bf16_t* __restrict__ out_act, float* __restrict__ out_z, const float* __restrict__ zprev,
+    const float* __restrict__ oscale, const float* __restrict__ oshift) {
   constexpr int KS = (9 * CIN + 31) / 32;
   constexpr int NT = (COUT + 15) / 16;
-  constexpr int CH = CIN / 8;
-  constexpr int MR = kConvRows;     // rows of the 16 x 16 tile per wavefront
-  constexpr int NTH = kConvThreads;
-  // The input halo, and after the products the FP32 results of the tile (HIDDEN and
-  // BWD), share one LDS buffer.  Result rows are padded by 4 floats so that the four
-  // lane groups of a store land in distinct banks.
-  constexpr int OS = COUT + 4;
-  // Halo positions are stored unpadded, 2 CIN bytes apart.  (Padding the 32-channel
-  // positions to 40 channels, meant to spread the A-fragment reads over the banks,
-  // was measured with SQ_LDS_BANK_CONFLICT to raise the conflict cycles by a third
-  // and left the time unchanged.)
-  constexpr int PS = CIN;
-  constexpr int kTileBytes = NZT * HALO * HALO * PS * 2;
-  constexpr int kOutBytes = MODE == MODE_LAST ? 0 : TILE * TILE * OS * 4;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kTileBytes > kOutBytes ? kTileBytes : kOutBytes];
-  bf16_t* tile = reinterpret_cast<bf16_t*>(lds);
-  const int sl = blockIdx.z, ty0 = blockIdx.y * TILE, tx0 = blockIdx.x * TILE;
-  const int zl = sl % D, zbase = sl - zl;  // slice within its lattice, first slice of the lattice
-  for (int q = threadIdx.x; q < NZT * HALO * HALO * CH; q += NTH) {
-    const int zs = q / (HALO * HALO * CH), r = q % (HALO * HALO * CH);
-    const int pix = r / CH, ch = r % CH;
-    const int hy = pix / HALO, hx = pix % HALO;
-    int gz = zl + zs - NZT / 2;
-    int gy = ty0 - 1 + hy;
-    int gx = tx0 - 1 + hx;
-    gz = gz < 0 ? gz + D : (gz >= D ? gz - D : gz);
-    gy = gy < 0 ? gy + H : (gy >= H ? gy - H : gy);
-    gx = gx < 0 ? gx + W : (gx >= W ? gx - W : gx);
-    const uint4 v =
-        *reinterpret_cast<const uint4*>(act + (((size_t)(zbase + gz) * H + gy) * W + gx) * CIN + ch * 8);
-    *reinterpret_cast<uint4*>(tile + (zs * HALO * HALO + pix) * PS + ch * 8) = v;
+  constexpr int MR = TILE * NT / (kConvThreads / 64);  // tile rows per wavefront
+  constexpr int kHalo = HALO * HALO * CIN * 2;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kHalo];
+  __shared__ __attribute__((aligned(16))) unsigned char lds2[kHalo];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int t = wv % NT, py0 = MR * (wv / NT), px = lane & 15, g = lane >> 4;
+  const int tiles_x = W / TILE, tiles_y = H / TILE, ntile = tiles_x * tiles_y;
+  HaloFetch<CIN, kConvThreads> halo;
+  halo.setup(W);
+  bf16x8 bw[NZT][KS];
+#pragma unroll
+  for (int kz = 0; kz < NZT; ++kz)
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      bw[kz][s] = *reinterpret_cast<const bf16x8*>(wpack + ((size_t)((kz * KS + s) * NT + t) * 64 + lane) * 8);
+  // the lane's four output channels (those past COUT are dropped) and their constants
+  const int co0 = 16 * t + 4 * g;
+  const bool live = co0 < COUT;
+  float4 bs = make_float4(0.0f, 0.0f, 0.0f, 0.0f), sc = bs, sh = bs;
+  if (live && MODE != MODE_BWD) bs = *reinterpret_cast<const float4*>(bias + co0);
+  if (live && MODE == MODE_LAST) {
+    sc = *reinterpret_cast<const float4*>(oscale + co0);
+    sh = *reinterpret_cast<const float4*>(oshift + co0);
   }
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  bf16x8 bw[KS][NT];
+  // 8 input channels: a K step holds 4 taps, lane group g the tap 4 s + g (zero past 9)
+  int tapoff[KS];
+  (void)tapoff;
 #pragma unroll
-  for (int s = 0; s < KS; ++s)
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-      bw[s][t] = *reinterpret_cast<const bf16x8*>(wpack + ((size_t)(s * NT + t) * 64 + lane) * 8);
-  __syncthreads();
+  for (int s = 0; s < KS; ++s) {
+    const int tap = min(4 * s + g, 8);
+    tapoff[s] = ((tap / 3) * HALO + tap % 3) * CIN;
+  }
 
-  f32x4 acc[MR][NT];
+  // planes of this workgroup: NZT == 1, tiles blockIdx.x, + gridDim.x, ... of all slices;
+  // else the slices z0 - 1 .. z1 of one tile column, outputs z0 .. z1 - 1
+  int np, tile = 0, z0 = 0, z1 = 0, zbase = 0;
+  if constexpr (NZT == 1) {
+    np = (S * ntile - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
+  } else {
+    const int nch = (D + zn - 1) / zn, chunk = blockIdx.x / ntile;
+    tile = blockIdx.x % ntile;
+    zbase = (chunk / nch) * D;
+    z0 = (chunk % nch) * zn;
+    z1 = min(z0 + zn, D);
+    np = z1 - z0 + 2;
+  }
+  auto where = [&](int j, int& sl, int& ty0, int& tx0) {  // plane j: its slice and tile
+    int tl = tile;
+    if constexpr (NZT == 1) {
+      const int id = blockIdx.x + j * gridDim.x;
+      sl = id / ntile;
+      tl = id % ntile;
+    } else {
+      const int z = z0 - 1 + j;
+      sl = zbase + (z < 0 ? z + D : (z >= D ? z - D : z));
+    }
+    ty0 = (tl / tiles_x) * TILE;
+    tx0 = (tl % tiles_x) * TILE;
+  };
+  auto fetch = [&](int j, unsigned char* buf) {
+    int sl, ty0, tx0;
+    where(j, sl, ty0, tx0);
+    halo(act + (size_t)sl * H * W * CIN, ty0, tx0, H, W, buf);
+  };
+  // acc[kz]: the output plane that this plane's tap kz belongs to (kz = NZT - 1: complete
+  // after this plane)
+  f32x4 acc[NZT][MR];
 #pragma unroll
-  for (int m = 0; m < MR; ++m)
+  for (int kz = 0; kz < NZT; ++kz)
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[m][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int m = 0; m < MR; ++m) acc[kz][m] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-  const int px = lane & 15, g = lane >> 4;
-#pragma unroll 1
-  for (int zs = 0; zs < NZT; ++zs) {
-    if (zs > 0) {  // weights of the next z-slab
+  // an output plane's rest: bias and activation, or the derivative's factor, and the stores
+  auto finish = [&](int j, const f32x4 (&v4)[MR], const float4* zp) __attribute__((always_inline)) {
+    int sl, ty0, tx0;
+    where(j, sl, ty0, tx0);
+    if (!live) return;
+    const size_t pos0 = ((size_t)sl * H + ty0 + py0) * W + tx0 + px;  // the lane's position in its first row
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+      const f32x4 v = v4[m];
+      const size_t pos = pos0 + (size_t)m * W;
+      if constexpr (MODE == MODE_LAST) {
+        const size_t plane_sz = (size_t)S * H * W;
+        float* o = out_z + (size_t)co0 * plane_sz + pos;
+        o[0] = (v[0] + bs.x) * sc.x + sh.x;
+        o[plane_sz] = (v[1] + bs.y) * sc.y + sh.y;
+        o[2 * plane_sz] = (v[2] + bs.z) * sc.z + sh.z;
+        o[3 * plane_sz] = (v[3] + bs.w) * sc.w + sh.w;
+      } else {
+        uint2 a;
+        if constexpr (MODE == MODE_HIDDEN) {
+          const float4 z = make_float4(v[0] + bs.x, v[1] + bs.y, v[2] + bs.z, v[3] + bs.w);
+          a = gelu_bf16(z);
+          if (out_z) *reinterpret_cast<float4*>(out_z + pos * COUT + co0) = z;
+        } else {
+          a.x = bf16_pair(v[0] * gelu_grad(zp[m].x), v[1] * gelu_grad(zp[m].y));
+          a.y = bf16_pair(v[2] * gelu_grad(zp[m].z), v[3] * gelu_grad(zp[m].w));
+        }
+        *reinterpret_cast<uint2*>(out_act + pos * COUT + co0) = a;
+      }
+    }
+  };
+  auto load_zprev = [&](int j, float4* zp) __attribute__((always_inline)) {
+    if constexpr (MODE == MODE_BWD) {
+      int sl, ty0, tx0;
+      where(j, sl, ty0, tx0);
+      const size_t pos0 = ((size_t)sl * H + ty0 + py0) * W + tx0 + px;
+#pragma unroll
+      for (int m = 0; m < MR; ++m)
+        zp[m] = *reinterpret_cast<const float4*>(zprev + (pos0 + (size_t)m * W) * COUT + co0);
+    }
+  };
+  // 3x3x3: two wavefronts share a SIMD.  The first four (one per SIMD) finish an output
+  // plane at the start of the next plane's turn and the other four at the end of its own,
+  // so that one's vector instructions run beside the other's products.
+  constexpr bool kTurns = NZT == 3;
+  const bool early = kTurns && wv < 4;
+  f32x4 held[kTurns ? MR : 1];
+  (void)held;
+
+  auto plane = [&](int j, const unsigned char* buf) __attribute__((always_inline)) {
+    const bf16_t* tz = reinterpret_cast<const bf16_t*>(buf);
+    const int jo = NZT == 1 ? j : j - 1;  // the output plane completed here
+    const bool done = NZT == 1 || j >= 2;
+    float4 zp[MODE == MODE_BWD ? MR : 1];
+    (void)zp;
+    if (kTurns && early) {
+      if constexpr (kTurns) {
+        if (j >= 3) {
+          load_zprev(jo - 1, zp);
+          finish(jo - 1, held, zp);
+        }
+      }
+    } else if (done) {
+      load_zprev(jo, zp);
+    }
+    if constexpr (CIN == 32) {
+#pragma unroll
+      for (int r = 0; r < MR + 2; ++r)
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) {
+          const bf16x8 a = *reinterpret_cast<const bf16x8*>(tz + ((py0 + r) * HALO + px + dx) * CIN + 8 * g);
+#pragma unroll
+          for (int dy = 0; dy < 3; ++dy) {
+            const int m = r - dy;
+            if (m < 0 || m >= MR) continue;
+#pragma unroll
+            for (int kz = 0; kz < NZT; ++kz)
+              acc[kz][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[kz][3 * dy + dx], a, acc[kz][m], 0, 0, 0);
+          }
+        }
+    } else {
 #pragma unroll
       for (int s = 0; s < KS; ++s)
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
-          bw[s][t] = *reinterpret_cast<const bf16x8*>(wpack + ((size_t)((zs * KS + s) * NT + t) * 64 + lane) * 8);
-    }
-    const bf16_t* tz = tile + zs * HALO * HALO * PS;
+        for (int m = 0; m < MR; ++m) {
+          bf16x8 a = *reinterpret_cast<const bf16x8*>(tz + ((py0 + m) * HALO + px) * CIN + tapoff[s]);
+          if (4 * s + 3 > 8 && 4 * s + g > 8) a = bf16x8{};  // zero padding of K
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-#pragma unroll
-      for (int m = 0; m < MR; ++m) {
-        const int py = MR * wv + m;
-        bf16x8 a;
-        if constexpr (CIN == 32) {
-          const int dy = s / 3, dx = s % 3;
-          a = *reinterpret_cast<const bf16x8*>(tz + ((py + dy) * HALO + px + dx) * PS + 8 * g);
-        } else {
-          const int tap = 4 * s + g;  // 8 input channels: 4 taps per K step
-          if (tap < 9) {
-            const int dy = tap / 3, dx = tap % 3;
-            a = *reinterpret_cast<const bf16x8*>(tz + ((py + dy) * HALO + px + dx) * PS);
-          } else {
-            a = bf16x8{};  // zero padding of K
-          }
+          for (int kz = 0; kz < NZT; ++kz)
+            acc[kz][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[kz][s], a, acc[kz][m], 0, 0, 0);
         }
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-          acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bw[s][t], acc[m][t], 0, 0, 0);
-      }
     }
-  }
-
-  if constexpr (MODE == MODE_LAST) {
-    // channel-major output: a lane's four results are four consecutive x of one channel
+    if constexpr (kTurns) {
+#pragma unroll
+      for (int m = 0; m < MR; ++m) held[m] = acc[NZT - 1][m];
+      if (!early && done) finish(jo, held, zp);
+    } else {
+      finish(jo, acc[0], zp);
+    }
+    // the next plane's taps belong one output plane further
 #pragma unroll
     for (int m = 0; m < MR; ++m) {
-      const int y = ty0 + MR * wv + m;
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int co = 16 * t + (lane & 15);
-        if (co >= COUT) continue;
-        const float b = bias[co], sc = oscale[co], sh = oshift[co];
-        float4 o;
-        o.x = (acc[m][t][0] + b) * sc + sh;
-        o.y = (acc[m][t][1] + b) * sc + sh;
-        o.z = (acc[m][t][2] + b) * sc + sh;
-        o.w = (acc[m][t][3] + b) * sc + sh;
-        *reinterpret_cast<float4*>(out_z + (((size_t)co * gridDim.z + sl) * H + y) * W + tx0 + 4 * g) = o;
-      }
+      for (int kz = NZT - 1; kz > 0; --kz) acc[kz][m] = acc[kz - 1][m];
+      acc[0][m] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
-  } else {
-    // channels-last outputs: stage the tile's results [position][channel] in LDS, then
-    // every thread finishes four consecutive channels of a position with 16-byte loads
-    // and stores
-    float* ob = reinterpret_cast<float*>(lds);
-    __syncthreads();  // every wavefront is done with the halo
-#pragma unroll
-    for (int m = 0; m < MR; ++m)
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int co = 16 * t + (lane & 15);
-        if (co >= COUT) continue;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) ob[((MR * wv + m) * TILE + 4 * g + r) * OS + co] = acc[m][t][r];
-      }
+  };
+  fetch(0, lds);
+  for (int j = 0; j < np; j += 2) {
+    lds_arrived();
+    __syncthreads();  // this plane is here; the previous one is fully consumed
+    if (j + 1 < np) fetch(j + 1, lds2);
+    plane(j, lds);
+    if (j + 1 >= np) break;
+    lds_arrived();
     __syncthreads();
-    constexpr int C4 = COUT / 4;
-    for (int q = threadIdx.x; q < TILE * TILE * C4; q += NTH) {
-      const int pos = q / C4, c0 = 4 * (q % C4);
-      const int y = ty0 + pos / TILE, x = tx0 + pos % TILE;
-      const size_t nhwc = (((size_t)sl * H + y) * W + x) * COUT + c0;
-      const float4 v = *reinterpret_cast<const float4*>(ob + pos * OS + c0);
-      float a[4];
-      if constexpr (MODE == MODE_HIDDEN) {
-        const float4 b = *reinterpret_cast<const float4*>(bias + c0);
-        const float4 z = make_float4(v.x + b.x, v.y + b.y, v.z + b.z, v.w + b.w);
-        a[0] = gelu(z.x), a[1] = gelu(z.y), a[2] = gelu(z.z), a[3] = gelu(z.w);
-        if (out_z) *reinterpret_cast<float4*>(out_z + nhwc) = z;
-      } else {
-        const float4 zp = *reinterpret_cast<const float4*>(zprev + nhwc);
-        a[0] = v.x * gelu_grad(zp.x), a[1] = v.y * gelu_grad(zp.y);
-        a[2] = v.z * gelu_grad(zp.z), a[3] = v.w * gelu_grad(zp.w);
-      }
-      uint2 packed;
-      packed.x = (unsigned)f2bf(a[0]) | ((unsigned)f2bf(a[1]) << 16);
-      packed.y = (unsigned)f2bf(a[2]) | ((unsigned)f2bf(a[3]) << 16);
-      *reinterpret_cast<uint2*>(out_act + nhwc) = packed;
+    if (j + 2 < np) fetch(j + 2, lds);
+    plane(j + 1, lds2);
+  }
+  if constexpr (kTurns) {
+    if (early) {
+      float4 zp[MODE == MODE_BWD ? MR : 1];
+      load_zprev(np - 2, zp);
+      finish(np - 2, held, zp);
     }
   }
 }
@@ -1011,10 +1143,31 @@ size_t packed_elems(int cin, int cout, int nzt) { return (size_t)nzt * ksteps(ci
 hipError_t launch_conv(int cin, int cout, int mode, int nzt, const bf16_t* act, const bf16_t* wpack,
                        const float* bias, int S, int D, int H, int W, bf16_t* out_act, float* out_z,
                        const float* zprev, const float* oscale, const float* oshift, hipStream_t s) {
-  const dim3 grd(W / TILE, H / TILE, S), blk(kConvThreads);
+  // 3x3: up to two workgroups per CU, the same number of tiles for each but the last few.
+  // 3x3x3 (one workgroup per CU): every tile column cut in z into nch shares of zn slices,
+  // the nch for which the rounds of workgroups over 256 CUs times a workgroup's time is
+  // least -- its slices, the two it stages beyond them, and about two slices' time to start
+  // (weights, first halo).
+  const int ntile = (W / TILE) * (H / TILE);
+  long long blocks;
+  int zn = 1;
+  if (nzt == 1) {
+    const long long jobs = (long long)S * ntile, per = (jobs + 511) / 512;
+    blocks = (jobs + per - 1) / per;
+  } else {
+    const long long cols = (long long)(S / D) * ntile;
+    long long best = -1;
+    for (int nch = 1; nch <= D && nch <= 64; ++nch) {
+      const int n = (D + nch - 1) / nch;
+      const long long cost = (cols * ((D + n - 1) / n) + 255) / 256 * (n + 4);
+      if (best < 0 || cost < best) best = cost, zn = n;
+    }
+    blocks = cols * ((D + zn - 1) / zn);
+  }
+  const dim3 grd((unsigned)blocks), blk(kConvThreads);
 #define CONV_CASE(CI, CO, M, Z)                                                                          \
   if (cin == CI && cout == CO && mode == M && nzt == Z) {                                               \
-    hipLaunchKernelGGL((k_conv<CI, CO, M, Z>), grd, blk, 0, s, act, wpack, bias, D, H, W, out_act, out_z, \
+    hipLaunchKernelGGL((k_conv<CI, CO, M, Z>), grd, blk, 0, s, act, wpack, bias, S, D, H, W, zn, out_act, out_z, \
                        zprev, oscale, oshift);                                                         \
     return hipGetLastError();                                                                          \
   }
