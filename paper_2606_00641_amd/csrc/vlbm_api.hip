@@ -248,6 +248,14 @@ void build_codec(vlbm_ctx* c) {
     }
 }
 
+// The totals of vlbm_moments: the moments pass's partials, and the central divergence's.
+hipError_t reduce_totals(vlbm_ctx* c, int NT, bool has_B, const double* partial, const double* partial2, double* tot) {
+  MaxMask m;
+  m.add(c->K + 2);
+  // without a field, slot K + 3 takes the moments pass's own (unused) zero
+  return launch_reduce(c->L, NT, partial, c->nblk, m, tot, has_B ? partial2 : nullptr, tot + c->K + 3);
+}
+
 }  // namespace
 
 // One step on the context's stream: faces, sweep (with the body, and its move), step + 1.
@@ -424,9 +432,9 @@ vlbm_status vlbm_create(const vlbm_params* p, vlbm_ctx** out) {
   }
   c->nblk = (int)std::min<long long>(1024, (c->N + 255) / 256);
   const int NT = c->K + 5;
-  hipError_t e = hipMalloc(&c->d_partial, sizeof(double) * (size_t)c->nblk * NT);
+  hipError_t e = hipMalloc(&c->d_partial, sizeof(double) * (size_t)c->nblk * std::max(NT, 3 * c->K));
   if (e == hipSuccess) e = hipMalloc(&c->d_partial2, sizeof(double) * (size_t)c->nblk);
-  if (e == hipSuccess) e = hipMalloc(&c->d_totals, sizeof(double) * (size_t)(NT + 2 * KMAX));
+  if (e == hipSuccess) e = hipMalloc(&c->d_totals, sizeof(double) * (size_t)(NT + 3 * KMAX));
   if (e != hipSuccess) {
     vlbm_destroy(c);
     return fail(nullptr, VLBM_ERR_OOM, "hipMalloc of reduction buffers: %s", hipGetErrorString(e));
@@ -514,42 +522,37 @@ vlbm_status vlbm_init_fields(vlbm_ctx* c, const void* Q, int q_on_device, int q_
   hipError_t e = hipSuccess;
   const bool codec = c->p.storage == VLBM_F16DEV || c->p.storage == VLBM_BF16DEV;
   if (codec) {
-    double* d_aux = c->d_totals + (c->K + 5);  // KMAX doubles after the totals
-    if (!c->rest_given) {
-      // Q_rest: domain mean with rho u (and G, H) set to zero
-      e = launch_field_reduce(c->L, c->N, c->K, dQ, q_is_f32, 0, nullptr, c->d_partial, c->nblk, d_aux);
-      double mean[KMAX];
-      if (e == hipSuccess) e = hipMemcpyAsync(mean, d_aux, sizeof(double) * c->K, hipMemcpyDeviceToHost, c->stream);
-      if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-      if (e == hipSuccess)
-        for (int k = 0; k < c->K; ++k)
-          c->rest_Q[k] = c->p.model == VLBM_NAVIER_CAUCHY
-                             ? (k <= 2 ? 0.0 : mean[k] / (double)c->N)  // momentum at rest, mean stress
-                             : c->p.model == VLBM_RESISTIVE_2D
-                                   ? ((k >= 1 && k <= 2) || k >= 6 ? 0.0 : mean[k] / (double)c->N)
-                                   : ((k >= 1 && k <= 3) || k >= 8 ? 0.0 : mean[k] / (double)c->N);
-    }
+    double* d_aux = c->d_totals + (c->K + 5);  // 3 KMAX doubles after the totals
     bool need_scale = false;
     for (int k = 0; k < c->K; ++k) need_scale |= !(c->p.scale[k] > 0.0);
-    if (e == hipSuccess && need_scale) {
-      double* d_rest = d_aux + KMAX;
-      double* d_dev = d_aux;
-      double dev[KMAX];
-      e = hipMemcpyAsync(d_rest, c->rest_Q, sizeof(double) * c->K, hipMemcpyHostToDevice, c->stream);
+    double stat[3 * KMAX];  // per variable: sum, max, max of the negated field
+    if (!c->rest_given || need_scale) {
+      e = launch_field_stats(c->L, c->N, c->K, dQ, q_is_f32, c->d_partial, c->nblk, d_aux);
       if (e == hipSuccess)
-        e = launch_field_reduce(c->L, c->N, c->K, dQ, q_is_f32, 1, d_rest, c->d_partial, c->nblk, d_dev);
-      if (e == hipSuccess) e = hipMemcpyAsync(dev, d_dev, sizeof(double) * c->K, hipMemcpyDeviceToHost, c->stream);
+        e = hipMemcpyAsync(stat, d_aux, sizeof(double) * 3 * c->K, hipMemcpyDeviceToHost, c->stream);
       if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-      if (e == hipSuccess)
-        for (int k = 0; k < c->K; ++k) {
-          if (c->p.scale[k] > 0.0) continue;
-          // a field uniform at the start (its spread no more than the rounding of its
-          // mean) is scaled by its own magnitude: the spread it develops later is
-          // unknown, and a scale set by rounding noise would saturate FP16 at once
-          const double mag = std::fabs(c->rest_Q[k]);
-          c->scale[k] = pow2_at_least(dev[k] > std::ldexp(mag, -20) ? dev[k] : mag);
-        }
     }
+    // Q_rest: domain mean with rho u (and G, H) set to zero
+    if (!c->rest_given && e == hipSuccess)
+      for (int k = 0; k < c->K; ++k)
+        c->rest_Q[k] = c->p.model == VLBM_NAVIER_CAUCHY
+                           ? (k <= 2 ? 0.0 : stat[3 * k] / (double)c->N)  // momentum at rest, mean stress
+                           : c->p.model == VLBM_RESISTIVE_2D
+                                 ? ((k >= 1 && k <= 2) || k >= 6 ? 0.0 : stat[3 * k] / (double)c->N)
+                                 : ((k >= 1 && k <= 3) || k >= 8 ? 0.0 : stat[3 * k] / (double)c->N);
+    if (e == hipSuccess && need_scale)
+      for (int k = 0; k < c->K; ++k) {
+        if (c->p.scale[k] > 0.0) continue;
+        // max |Q_k - rest|: the rounded difference grows with Q_k, so an extreme has it
+        // (0 for a field of NaN only, whose extremes stay -infinity)
+        const double hi = stat[3 * k + 1], lo = -stat[3 * k + 2];
+        const double dev = hi < lo ? 0.0 : std::max(std::fabs(hi - c->rest_Q[k]), std::fabs(lo - c->rest_Q[k]));
+        // a field uniform at the start (its spread no more than the rounding of its
+        // mean) is scaled by its own magnitude: the spread it develops later is
+        // unknown, and a scale set by rounding noise would saturate FP16 at once
+        const double mag = std::fabs(c->rest_Q[k]);
+        c->scale[k] = pow2_at_least(dev > std::ldexp(mag, -20) ? dev : mag);
+      }
     if (e == hipSuccess) build_codec(c);
   }
   if (e == hipSuccess) e = launch_init(c->L, c->g, c->ph, c->cd, dQ, q_is_f32);
@@ -582,41 +585,48 @@ vlbm_status vlbm_moments(vlbm_ctx* c, void* Q_out, int out_on_device, int out_is
   if (!c) return VLBM_ERR_ARG;
   if (!c->initialized) return fail(c, VLBM_ERR_STATE, "vlbm_moments before vlbm_init_fields");
   const size_t nq = (size_t)c->K * c->N;
-  double* Qd;
-  if (Q_out && out_on_device && !out_is_f32) {
-    Qd = static_cast<double*>(Q_out);
+  const bool has_B = c->p.model == VLBM_IDEAL || c->p.model == VLBM_RESISTIVE || c->p.model == VLBM_RESISTIVE_2D;
+  const int bx = c->p.model == VLBM_RESISTIVE_2D ? 4 : 5;
+  // the whole FP64 field only where it is the result or goes to the host
+  const bool direct32 = Q_out && out_on_device && out_is_f32;
+  const bool field = Q_out && !direct32;
+  FieldsOut out{nullptr, direct32 ? static_cast<float*>(Q_out) : nullptr, nullptr};
+  if (field && out_on_device) {
+    out.q64 = static_cast<double*>(Q_out);
   } else {
-    if (!c->d_Q) VLBM_HIP(c, hipMalloc(&c->d_Q, sizeof(double) * nq));
-    Qd = c->d_Q;
+    const size_t need = field ? (size_t)c->K : (has_B ? (size_t)c->D : 0);  // planes of scratch
+    if (need > c->q_planes) {
+      if (c->d_Q) (void)hipFree(c->d_Q);
+      c->d_Q = nullptr;
+      c->q_planes = 0;
+      VLBM_HIP(c, hipMalloc(&c->d_Q, sizeof(double) * need * (size_t)c->N));
+      c->q_planes = need;
+    }
+    (field ? out.q64 : out.b64) = has_B || field ? c->d_Q : nullptr;
   }
+  const double* B = out.q64 ? out.q64 + (size_t)bx * c->N : out.b64;
   const int NT = c->K + 5;
   const int par = (int)(c->step & 1);
-  VLBM_HIP(c, launch_moments(c->L, c->g, c->ph, c->cd, par, Qd, c->d_partial, c->nblk));
-  const bool has_B = c->p.model == VLBM_IDEAL || c->p.model == VLBM_RESISTIVE || c->p.model == VLBM_RESISTIVE_2D;
-  if (has_B) VLBM_HIP(c, launch_divc(c->L, c->g, Qd, c->d_partial2, c->nblk));
-  VLBM_HIP(c, launch_reduce(c->L, NT, c->d_partial, c->nblk, 1u << (c->K + 2), c->d_totals));
-  if (has_B) VLBM_HIP(c, launch_reduce(c->L, 1, c->d_partial2, c->nblk, 0u, c->d_totals + c->K + 3));
+  VLBM_HIP(c, launch_moments(c->L, c->g, c->ph, c->cd, par, out, c->d_partial, c->nblk));
+  if (has_B) VLBM_HIP(c, launch_divc(c->L, c->g, B, c->d_partial2, c->nblk));
+  VLBM_HIP(c, reduce_totals(c, NT, has_B, c->d_partial, c->d_partial2, c->d_totals));
   double tot[KMAX + 5];
   VLBM_HIP(c, hipMemcpyAsync(tot, c->d_totals, sizeof(double) * NT, hipMemcpyDeviceToHost, c->stream));
-  VLBM_HIP(c, hipStreamSynchronize(c->stream));
-  if (!has_B) tot[c->K + 3] = 0.0;  // no field, no divergence
-  if (Q_out && Qd != Q_out) {
+  std::vector<double> h;
+  if (field && !out_on_device) {
+    void* dst = Q_out;
     if (out_is_f32) {
-      if (out_on_device) {
-        VLBM_HIP(c, launch_to_f32(c->stream, Qd, static_cast<float*>(Q_out), (long long)nq));
-      } else {
-        std::vector<double> h(nq);
-        VLBM_HIP(c, hipMemcpyAsync(h.data(), Qd, sizeof(double) * nq, hipMemcpyDeviceToHost, c->stream));
-        VLBM_HIP(c, hipStreamSynchronize(c->stream));
-        float* o = static_cast<float*>(Q_out);
-        for (size_t j = 0; j < nq; ++j) o[j] = (float)h[j];
-      }
-    } else {
-      VLBM_HIP(c, hipMemcpyAsync(Q_out, Qd, sizeof(double) * nq,
-                                 out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, c->stream));
+      h.resize(nq);
+      dst = h.data();
     }
+    VLBM_HIP(c, hipMemcpyAsync(dst, out.q64, sizeof(double) * nq, hipMemcpyDeviceToHost, c->stream));
   }
   VLBM_HIP(c, hipStreamSynchronize(c->stream));
+  if (!has_B) tot[c->K + 3] = 0.0;  // no field, no divergence
+  if (!h.empty()) {
+    float* o = static_cast<float*>(Q_out);
+    for (size_t j = 0; j < nq; ++j) o[j] = (float)h[j];
+  }
   if (totals) std::memcpy(totals, tot, sizeof(double) * NT);
   bool finite = true;
   for (int j = 0; j < NT; ++j) finite = finite && std::isfinite(tot[j]);
@@ -684,11 +694,11 @@ vlbm_status vlbm_moments_noalloc(vlbm_ctx* c, double* Q_out, double* totals) {
   double* tot_d = partial2 + c->nblk;
   double* Qd = static_cast<double*>(Q_out);
   const int par = (int)(c->step & 1);
-  VLBM_HIP(c, launch_moments(c->L, c->g, c->ph, c->cd, par, Qd, partial, c->nblk));
+  VLBM_HIP(c, launch_moments(c->L, c->g, c->ph, c->cd, par, FieldsOut{Qd, nullptr, nullptr}, partial, c->nblk));
   const bool has_B = c->p.model == VLBM_IDEAL || c->p.model == VLBM_RESISTIVE || c->p.model == VLBM_RESISTIVE_2D;
-  if (has_B) VLBM_HIP(c, launch_divc(c->L, c->g, Qd, partial2, c->nblk));
-  VLBM_HIP(c, launch_reduce(c->L, NT, partial, c->nblk, 1u << (c->K + 2), tot_d));
-  if (has_B) VLBM_HIP(c, launch_reduce(c->L, 1, partial2, c->nblk, 0u, tot_d + c->K + 3));
+  const int bx = c->p.model == VLBM_RESISTIVE_2D ? 4 : 5;
+  if (has_B) VLBM_HIP(c, launch_divc(c->L, c->g, Qd + (size_t)bx * c->N, partial2, c->nblk));
+  VLBM_HIP(c, reduce_totals(c, NT, has_B, partial, partial2, tot_d));
   double tot[KMAX + 5];
   VLBM_HIP(c, hipMemcpyAsync(tot, tot_d, sizeof(double) * NT, hipMemcpyDeviceToHost, c->stream));
   VLBM_HIP(c, hipStreamSynchronize(c->stream));
@@ -772,7 +782,7 @@ vlbm_status vlbm_body_loads(vlbm_ctx* c, double* loads) {
   hlbm_box(c, b.t, b.box);
   const int par = (int)(c->step & 1);
   VLBM_HIP(c, launch_body_loads(c->L, c->g, c->ph, c->cd, par, b, c->d_partial, c->nblk));
-  VLBM_HIP(c, launch_reduce(c->L, 8, c->d_partial, c->nblk, 0u, c->d_totals));
+  VLBM_HIP(c, launch_reduce(c->L, 8, c->d_partial, c->nblk, MaxMask{}, c->d_totals));
   VLBM_HIP(c, hipMemcpyAsync(loads, c->d_totals, 8 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   VLBM_HIP(c, hipStreamSynchronize(c->stream));
   return VLBM_OK;

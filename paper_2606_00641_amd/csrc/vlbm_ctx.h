@@ -26,10 +26,11 @@ struct vlbm_ctx {
   double scale[vlbm::KMAX] = {};
   bool rest_given = false;
   int nblk = 0;
-  double* d_partial = nullptr;   // [nblk][K+5]
+  double* d_partial = nullptr;   // [nblk][max(K+5, 3K)]
   double* d_partial2 = nullptr;  // [nblk]
-  double* d_totals = nullptr;    // [K+5] totals, then 2 x KMAX codec scratch
-  double* d_Q = nullptr;         // [K][N] moments scratch (lazy)
+  double* d_totals = nullptr;    // [K+5] totals, then 3 x KMAX codec scratch
+  double* d_Q = nullptr;         // [q_planes][N] moments scratch (lazy, grown)
+  size_t q_planes = 0;
   bool has_faces = false;         // some face is not periodic
   vlbm::Inflow inflow{};
   vlbm::Body body{};              // geometry; t and box set per launch

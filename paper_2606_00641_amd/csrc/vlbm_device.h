@@ -256,8 +256,6 @@ struct HlbmTarget {
   }
 };
 
-dim3 cell_grid(const Grid& g, int bx) { return dim3((g.nx + bx - 1) / bx, g.ny, g.nz); }
-
 // dispatch on (storage, dim, model) for functions templated <ST, D, MODEL>
 template <template <int, int, int> class Fn, typename... A>
 hipError_t dispatch(const Launch& L, A&&... args) {

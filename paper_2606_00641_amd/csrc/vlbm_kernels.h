@@ -135,33 +135,42 @@ hipError_t launch_net_input(const Launch& L, const Grid& g, const Codec& cd, int
 hipError_t launch_init(const Launch& L, const Grid& g, const Phys& ph, const Codec& cd,
                        const void* Q, int q_is_f32);
 
-// Moments at the given parity: Qout [K][N] FP64 (device), per-block partial sums
-// [nblk][K+5] (sum Q_k, sum d, sum d^2, max |d|, unused, bad count).
+// What the moments pass writes (device; NULL: not): all moments in FP64 or FP32, [K][N],
+// and the FP64 field of B alone, [dim][N].
+struct FieldsOut {
+  double* q64;
+  float* q32;
+  double* b64;
+};
+// Moments at the given parity, and per-block partial sums [nblk][K+5] (sum Q_k, sum d,
+// sum d^2, max |d|, unused, bad count).
 hipError_t launch_moments(const Launch& L, const Grid& g, const Phys& ph, const Codec& cd,
-                          int parity, double* Qout, double* partial, int nblk);
-// Central div B of the moment field: per-block partial sums of its square [nblk].
-hipError_t launch_divc(const Launch& L, const Grid& g, const double* Qout, double* partial,
-                       int nblk);
-// Fixed-order reduction of per-block partials [nblk][n] into out[n] (device);
-// slots whose bit is set in maxmask take the max, the others the sum.
+                          int parity, const FieldsOut& out, double* partial, int nblk);
+// Central div B of the FP64 field B [dim][N]: per-block partial sums of its square [nblk].
+hipError_t launch_divc(const Launch& L, const Grid& g, const double* B, double* partial, int nblk);
 // Loads on the homogenized body at time b.t over b.box: nblk block partials of
 // (force[3], torque[3], energy, magnetic flux), to be summed with launch_reduce.
 hipError_t launch_body_loads(const Launch& L, const Grid& g, const Phys& ph, const Codec& cd, int parity,
                              const Body& b, double* partial, int nblk);
-hipError_t launch_reduce(const Launch& L, int n, const double* partial, int nblk, unsigned maxmask,
-                         double* out);
+// Slots of a reduction that take the maximum (the others the sum).
+struct MaxMask {
+  unsigned w[4] = {0, 0, 0, 0};
+  __host__ __device__ bool has(int j) const { return (w[j >> 5] >> (j & 31)) & 1u; }
+  void add(int j) { w[j >> 5] |= 1u << (j & 31); }
+};
+// Fixed-order reduction of per-block partials [nblk][n] into out[n] (device, n <= 128), and
+// of the sums partial2 [nblk], if given, into *out2.
+hipError_t launch_reduce(const Launch& L, int n, const double* partial, int nblk, MaxMask maxmask,
+                         double* out, const double* partial2 = nullptr, double* out2 = nullptr);
 
 // Decoded populations at listed cells: out[n][K][NQ] FP64.
 hipError_t launch_gather(const Launch& L, const Grid& g, const Codec& cd, int parity, int K,
                          const long long* cells, long long n, double* out);
 
-// Per-variable sum (mode 0) or max |Q_k - rest_k| (mode 1) over a device field
-// Q [K][N] (FP64 or FP32); result out[K] FP64 (device).
-hipError_t launch_field_reduce(const Launch& L, long long N, int K, const void* Q, int q_is_f32,
-                               int mode, const double* rest, double* partial, int nblk, double* out);
-
-// FP64 -> FP32 conversion of n values.
-hipError_t launch_to_f32(hipStream_t s, const double* in, float* out, long long n);
+// Per variable of a device field Q [K][N] (FP64 or FP32) its sum, its largest value and its
+// largest negated value, FP64 out[3 K] (device); partial: 3 K nblk doubles.
+hipError_t launch_field_stats(const Launch& L, long long N, int K, const void* Q, int q_is_f32, double* partial,
+                              int nblk, double* out);
 
 // Streaming 16-byte copy.
 hipError_t launch_copy(hipStream_t s, void* dst, const void* src, size_t bytes);

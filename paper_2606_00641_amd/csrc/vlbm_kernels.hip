@@ -179,6 +179,9 @@ __global__ __launch_bounds__(256) void k_refill(const Grid g, const Phys ph, con
 // ---------------------------------------------------------------------------
 // init: f := f^eq(Q), natural layout
 // ---------------------------------------------------------------------------
+// Every cell by itself, so threads take consecutive cells of the whole lattice (row
+// workgroups left lanes idle on rows they do not tile: 190 x 113 x 77 in FP32 113 us, flat
+// 74 us).  Two cells per thread in 16-bit storage gained nothing (4.1 ms on 512^3 either way).
 template <int ST, int D, int MODEL, typename QT>
 __global__ __launch_bounds__(256) void k_init(const Grid g, const Phys ph, const Codec cd,
                                               const QT* __restrict__ Qin) {
@@ -187,10 +190,10 @@ __global__ __launch_bounds__(256) void k_init(const Grid g, const Phys ph, const
   using R = typename S::R;
   constexpr int NQ = 2 * D + 1;
   constexpr int K = kNVars<MODEL>;
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= g.nx) return;
-  const unsigned c = (unsigned)x + (unsigned)g.nx * (blockIdx.y + (unsigned)g.ny * blockIdx.z);
-  const size_t N = (size_t)g.nx * g.ny * g.nz;
+  const unsigned n = (unsigned)g.nx * (unsigned)g.ny * (unsigned)g.nz;
+  const unsigned c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= n) return;
+  const size_t N = n;
   T* __restrict__ F = static_cast<T*>(g.f);
   R Q[K];
 #pragma unroll
@@ -243,50 +246,71 @@ __device__ void block_reduce(double (&v)[NMAX], int n, unsigned maxmask, double*
   }
 }
 
+// Moments and FP64 diagnostics.  out names what is written: the FP64 field, the FP32 field,
+// and the FP64 field of B alone for the central divergence where the whole FP64 field is
+// not asked for (writing it all and converting it in a second pass took 2.9 ms more on
+// 512^3 in FP32 storage).  Bound by HBM: the populations once and the fields written.
+// 32-bit cell arithmetic: the 64-bit divisions held 512^3 in FP16 at 8.9 ms (now 4.6 ms,
+// 4.9 TB/s) and 256^3 x 26 in FP32 at 6.1 (now 2.9 ms, 5.3 TB/s).  Two cells per thread in
+// 16-bit storage took 25 ms (356 VGPRs).
 template <int ST, int D, int MODEL>
 __global__ __launch_bounds__(kReduceThreads) void k_moments(const Grid g, const Phys ph,
-                                                            const Codec cd, int parity,
-                                                            double* __restrict__ Qout,
+                                                            const Codec cd, int parity, const FieldsOut out,
                                                             double* __restrict__ partial) {
   using S = Store<ST>;
   using T = typename S::T;
   constexpr int NQ = 2 * D + 1;
   constexpr int K = kNVars<MODEL>;
   constexpr int NT = K + 5;
+  constexpr bool PK = MODEL == 1 && sizeof(T) == 2;
+  constexpr int bx = kBx<MODEL>;
   const T* __restrict__ F = static_cast<const T*>(g.f);
-  const size_t N = (size_t)g.nx * g.ny * g.nz;
+  const unsigned N = (unsigned)g.nx * (unsigned)g.ny * (unsigned)g.nz;
   double acc[NT];
 #pragma unroll
   for (int j = 0; j < NT; ++j) acc[j] = 0.0;
-  for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < N;
-       c += (size_t)gridDim.x * blockDim.x) {
-    const int x = (int)(c % g.nx);
-    const int y = (int)((c / g.nx) % g.ny);
-    const int z = (int)(c / ((size_t)g.nx * g.ny));
+  for (unsigned c = blockIdx.x * blockDim.x + threadIdx.x; c < N; c += gridDim.x * blockDim.x) {
+    auto write = [&](int k, double q) {
+      if (out.q64) out.q64[(size_t)k * N + c] = q;
+      if (out.q32) out.q32[(size_t)k * N + c] = (float)q;
+      if (out.b64 && k >= bx && k < bx + D) out.b64[(size_t)(k - bx) * N + c] = q;
+    };
     if (g.mask && (g.mask[c] & kSolid)) {  // inside the body: no fluid state
 #pragma unroll
-      for (int k = 0; k < K; ++k) Qout[(size_t)k * N + c] = 0.0;
+      for (int k = 0; k < K; ++k) write(k, 0.0);
       continue;
     }
+    const unsigned row = c / (unsigned)g.nx, x = c - row * (unsigned)g.nx;
+    const unsigned z = row / (unsigned)g.ny, y = row - z * (unsigned)g.ny;
     unsigned np[3], nm[3];
-    neighbours<D>(g, x, y, z, (unsigned)c, np, nm);
+    neighbours<D>(g, (int)x, (int)y, (int)z, c, np, nm);
+    auto cell_of = [&](int i) {
+      return (parity == 0 || i == 0) ? c : ((i & 1) ? nm[(i - 1) >> 1] : np[(i - 1) >> 1]);
+    };
+    auto slot_of = [&](int i) { return parity == 0 ? i : opposite(i); };
     double Q[K];
     double Jb[3] = {0.0, 0.0, 0.0};
+    auto add = [&](int k, int i, double v) {
+      Q[k] += v;
+      if (k >= bx && k < bx + D && i > 0 && ((i - 1) >> 1) == k - bx) Jb[k - bx] += (i & 1) ? v : -v;
+    };
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      double q = 0.0;
+    for (int k = 0; k < K; ++k) Q[k] = 0.0;
+    if constexpr (PK) {
 #pragma unroll
-      for (int i = 0; i < NQ; ++i) {
-        const unsigned src = (parity == 0 || i == 0) ? (unsigned)c
-                             : ((i & 1) ? nm[(i - 1) >> 1] : np[(i - 1) >> 1]);
-        const int slot = parity == 0 ? i : opposite(i);
-        const double v = S::dec64(F[pop_index(g, NQ, k, slot, src)], cd, k * NQ + i);
-        q += v;
-        constexpr int bx = kBx<MODEL>;
-        if (k >= bx && k < bx + D && i > 0 && ((i - 1) >> 1) == k - bx) Jb[k - bx] += (i & 1) ? v : -v;
-      }
-      Q[k] = q;
-      Qout[(size_t)k * N + c] = q;
+      for (int p = 0; p < K / 2; ++p)
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+          const unsigned v = static_cast<const unsigned*>(g.f)[(size_t)(p * NQ + slot_of(i)) * g.stride + cell_of(i)];
+          add(2 * p, i, S::dec64((T)(v & 0xffffu), cd, 2 * p * NQ + i));
+          add(2 * p + 1, i, S::dec64((T)(v >> 16), cd, (2 * p + 1) * NQ + i));
+        }
+    } else {
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int i = 0; i < NQ; ++i)
+          add(k, i, S::dec64(F[(size_t)(k * NQ + slot_of(i)) * g.stride + cell_of(i)], cd, k * NQ + i));
     }
     double P[K][3], Sv[K], dl;
     if (ph.source == 1) {
@@ -297,11 +321,10 @@ __global__ __launch_bounds__(kReduceThreads) void k_moments(const Grid g, const 
       for (int k = 0; k < K; ++k) q[k] = Q[k] + 0.5 * Sv[k];
       flux_source<double, D, MODEL>(q, Jb, ph, P, Sv, dl);
 #pragma unroll
-      for (int k = 0; k < K; ++k) {
-        Q[k] += 0.5 * Sv[k];
-        Qout[(size_t)k * N + c] = Q[k];
-      }
+      for (int k = 0; k < K; ++k) Q[k] += 0.5 * Sv[k];
     }
+#pragma unroll
+    for (int k = 0; k < K; ++k) write(k, Q[k]);
     const bool bad = flux_source<double, D, MODEL>(Q, Jb, ph, P, Sv, dl);
 #pragma unroll
     for (int k = 0; k < K; ++k) acc[k] += Q[k];
@@ -391,58 +414,65 @@ __global__ __launch_bounds__(kReduceThreads) void k_body_loads(const Grid g, con
   block_reduce<8>(acc, 8, 0u, partial + (size_t)blockIdx.x * 8);
 }
 
-// bx: index of B_x in the moment field
+// Bf: the FP64 field of B, [D][N]
 template <int D>
-__global__ __launch_bounds__(kReduceThreads) void k_divc(const Grid g, const double* __restrict__ Qm, int bx,
+__global__ __launch_bounds__(kReduceThreads) void k_divc(const Grid g, const double* __restrict__ Bf,
                                                          double* __restrict__ partial) {
-  const size_t N = (size_t)g.nx * g.ny * g.nz;
+  const unsigned N = (unsigned)g.nx * (unsigned)g.ny * (unsigned)g.nz;
   double acc[1] = {0.0};
-  for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < N;
-       c += (size_t)gridDim.x * blockDim.x) {
-    const int x = (int)(c % g.nx);
-    const int y = (int)((c / g.nx) % g.ny);
-    const int z = (int)(c / ((size_t)g.nx * g.ny));
+  for (unsigned c = blockIdx.x * blockDim.x + threadIdx.x; c < N; c += gridDim.x * blockDim.x) {
+    const unsigned row = c / (unsigned)g.nx, x = c - row * (unsigned)g.nx;
+    const unsigned z = row / (unsigned)g.ny, y = row - z * (unsigned)g.ny;
     unsigned np[3], nm[3];
-    neighbours<D>(g, x, y, z, (unsigned)c, np, nm);
+    neighbours<D>(g, (int)x, (int)y, (int)z, c, np, nm);
     double dv = 0.0;
 #pragma unroll
-    for (int a = 0; a < D; ++a) dv += 0.5 * (Qm[(size_t)(bx + a) * N + np[a]] - Qm[(size_t)(bx + a) * N + nm[a]]);
+    for (int a = 0; a < D; ++a) dv += 0.5 * (Bf[(size_t)a * N + np[a]] - Bf[(size_t)a * N + nm[a]]);
     acc[0] += dv * dv;
   }
   block_reduce<1>(acc, 1, 0u, partial + blockIdx.x);
 }
 
-template <int NMAX>
+// One workgroup per slot: slot j < n reduces partial[.][j] into out[j] (thread t takes
+// workgroups t, t + 256, ... in that order); slot n, if partial2 is given, the sums
+// partial2[.] into *out2, which may be one of out's places.  (All slots in one workgroup, their accumulators indexed at run time, took
+// 8-20 us.)
 __global__ __launch_bounds__(kReduceThreads) void k_reduce(int n, const double* __restrict__ partial,
-                                                           int nblk, unsigned maxmask,
-                                                           double* __restrict__ out) {
-  double acc[NMAX];
-#pragma unroll
-  for (int j = 0; j < NMAX; ++j) acc[j] = 0.0;
-  for (int b = threadIdx.x; b < nblk; b += blockDim.x)
-    for (int j = 0; j < n; ++j) {
-      const double v = partial[(size_t)b * n + j];
-      acc[j] = ((maxmask >> j) & 1u) ? fmax(acc[j], v) : acc[j] + v;
-    }
-  block_reduce<NMAX>(acc, n, maxmask, out);
+                                                           int nblk, MaxMask maxmask, double* __restrict__ out,
+                                                           const double* __restrict__ partial2,
+                                                           double* __restrict__ out2) {
+  const int j = blockIdx.x;
+  if (partial2 && out + j == out2) return;  // the other sums' place
+  const bool second = j == n, mx = !second && maxmask.has(j);
+  const double* p = second ? partial2 : partial + j;
+  const size_t stride = second ? 1 : (size_t)n;
+  double acc[1] = {mx ? -INFINITY : 0.0};
+  for (int b = threadIdx.x; b < nblk; b += blockDim.x) {
+    const double v = p[(size_t)b * stride];
+    acc[0] = mx ? fmax(acc[0], v) : acc[0] + v;
+  }
+  block_reduce<1>(acc, 1, mx ? 1u : 0u, second ? out2 : out + j);
 }
 
-// per-variable sum (mode 0) or max |Q_k - rest_k| (mode 1) over the field
-template <int NMAX, typename QT>
-__global__ __launch_bounds__(kReduceThreads) void k_field_reduce(const QT* __restrict__ Q, long long N,
-                                                                 int K, int mode,
-                                                                 const double* __restrict__ rest,
-                                                                 double* __restrict__ partial) {
-  double acc[NMAX];
-#pragma unroll
-  for (int j = 0; j < NMAX; ++j) acc[j] = 0.0;
-  for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < N;
-       c += (long long)gridDim.x * blockDim.x)
-    for (int k = 0; k < K; ++k) {
-      const double v = (double)Q[(size_t)k * N + c];
-      acc[k] = mode == 0 ? acc[k] + v : fmax(acc[k], fabs(v - rest[k]));
-    }
-  block_reduce<NMAX>(acc, K, mode == 0 ? 0u : 0xffffffffu, partial + (size_t)blockIdx.x * K);
+// Statistics of a field Q [K][N]: per variable k (blockIdx.y) and workgroup the sum, the
+// largest value and the largest negated value, partial[(b K + k) 3 + 0..2].  One variable
+// per workgroup, so that the accumulators stay in registers (all K in every thread, indexed
+// at run time, read 4.3 GB in 3.4 ms).
+template <typename QT>
+__global__ __launch_bounds__(kReduceThreads) void k_field_stats(const QT* __restrict__ Q, unsigned N,
+                                                                double* __restrict__ partial) {
+  const int k = blockIdx.y, K = gridDim.y;
+  const QT* __restrict__ q = Q + (size_t)k * N;
+  double sum = 0.0, hi = -INFINITY, lo = -INFINITY;
+#pragma unroll 4
+  for (unsigned c = blockIdx.x * blockDim.x + threadIdx.x; c < N; c += gridDim.x * blockDim.x) {
+    const double v = (double)q[c];
+    sum += v;
+    hi = fmax(hi, v);
+    lo = fmax(lo, -v);
+  }
+  double acc[3] = {sum, hi, lo};
+  block_reduce<3>(acc, 3, 6u, partial + ((size_t)blockIdx.x * K + k) * 3);
 }
 
 template <int ST, int D>
@@ -465,12 +495,6 @@ __global__ void k_gather(const Grid g, const Codec cd, int parity, int K,
   const int slot = parity == 0 ? i : opposite(i);
   const T* F = static_cast<const T*>(g.f);
   out[t] = S::dec64(F[pop_index(g, NQ, k, slot, src)], cd, k * NQ + i);
-}
-
-__global__ void k_to_f32(const double* __restrict__ in, float* __restrict__ out, long long n) {
-  for (long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x; t < n;
-       t += (long long)gridDim.x * blockDim.x)
-    out[t] = (float)in[t];
 }
 
 // One 16-byte element per thread and no grid-stride loop: the fastest plain copy
@@ -516,7 +540,8 @@ hipError_t boundary(const Launch& L, const Grid& g, const Phys& ph, const Codec&
 template <int ST, int D, int MODEL>
 hipError_t init_t(const Launch& L, const Grid& g, const Phys& ph, const Codec& cd, const void* Q,
                   int f32) {
-  const dim3 grd = cell_grid(g, L.block_x), blk(L.block_x);
+  const long long n = (long long)g.nx * g.ny * g.nz;
+  const dim3 grd((unsigned)((n + 255) / 256)), blk(256);
   if (f32)
     hipLaunchKernelGGL((k_init<ST, D, MODEL, float>), grd, blk, 0, L.stream, g, ph, cd,
                        static_cast<const float*>(Q));
@@ -528,9 +553,9 @@ hipError_t init_t(const Launch& L, const Grid& g, const Phys& ph, const Codec& c
 
 template <int ST, int D, int MODEL>
 hipError_t moments_t(const Launch& L, const Grid& g, const Phys& ph, const Codec& cd, int parity,
-                     double* Qout, double* partial, int nblk) {
+                     const FieldsOut& out, double* partial, int nblk) {
   hipLaunchKernelGGL((k_moments<ST, D, MODEL>), dim3(nblk), dim3(kReduceThreads), 0, L.stream, g,
-                     ph, cd, parity, Qout, partial);
+                     ph, cd, parity, out, partial);
   return hipGetLastError();
 }
 
@@ -556,8 +581,8 @@ struct InitFn {
 template <int ST, int D, int M>
 struct MomentsFn {
   static hipError_t run(const Launch& L, const Grid& g, const Phys& ph, const Codec& cd, int par,
-                        double* Qout, double* partial, int nblk) {
-    return moments_t<ST, D, M>(L, g, ph, cd, par, Qout, partial, nblk);
+                        const FieldsOut& out, double* partial, int nblk) {
+    return moments_t<ST, D, M>(L, g, ph, cd, par, out, partial, nblk);
   }
 };
 
@@ -603,16 +628,15 @@ hipError_t launch_mask(const Launch& L, const Grid& g, const Body& b, int pass, 
 }
 
 hipError_t launch_moments(const Launch& L, const Grid& g, const Phys& ph, const Codec& cd,
-                          int parity, double* Qout, double* partial, int nblk) {
-  return dispatch<MomentsFn>(L, g, ph, cd, parity, Qout, partial, nblk);
+                          int parity, const FieldsOut& out, double* partial, int nblk) {
+  return dispatch<MomentsFn>(L, g, ph, cd, parity, out, partial, nblk);
 }
 
-hipError_t launch_divc(const Launch& L, const Grid& g, const double* Qout, double* partial, int nblk) {
-  const int bx = L.model == 4 ? kBx<4> : kBx<0>;
+hipError_t launch_divc(const Launch& L, const Grid& g, const double* B, double* partial, int nblk) {
   if (L.dim == 2)
-    hipLaunchKernelGGL((k_divc<2>), dim3(nblk), dim3(kReduceThreads), 0, L.stream, g, Qout, bx, partial);
+    hipLaunchKernelGGL((k_divc<2>), dim3(nblk), dim3(kReduceThreads), 0, L.stream, g, B, partial);
   else
-    hipLaunchKernelGGL((k_divc<3>), dim3(nblk), dim3(kReduceThreads), 0, L.stream, g, Qout, bx, partial);
+    hipLaunchKernelGGL((k_divc<3>), dim3(nblk), dim3(kReduceThreads), 0, L.stream, g, B, partial);
   return hipGetLastError();
 }
 
@@ -630,11 +654,11 @@ hipError_t launch_body_loads(const Launch& L, const Grid& g, const Phys& ph, con
   return hipGetLastError();
 }
 
-hipError_t launch_reduce(const Launch& L, int n, const double* partial, int nblk, unsigned maxmask,
-                         double* out) {
-  if (n > 32) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_reduce<32>), dim3(1), dim3(kReduceThreads), 0, L.stream, n, partial, nblk,
-                     maxmask, out);
+hipError_t launch_reduce(const Launch& L, int n, const double* partial, int nblk, MaxMask maxmask,
+                         double* out, const double* partial2, double* out2) {
+  if (n > 128) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_reduce, dim3((unsigned)(n + (partial2 ? 1 : 0))), dim3(kReduceThreads), 0, L.stream, n, partial,
+                     nblk, maxmask, out, partial2, out2);
   return hipGetLastError();
 }
 
@@ -649,23 +673,20 @@ hipError_t launch_gather(const Launch& L, const Grid& g, const Codec& cd, int pa
   }
 }
 
-hipError_t launch_field_reduce(const Launch& L, long long N, int K, const void* Q, int q_is_f32,
-                               int mode, const double* rest, double* partial, int nblk, double* out) {
-  if (K > 32) return hipErrorInvalidValue;
+hipError_t launch_field_stats(const Launch& L, long long N, int K, const void* Q, int q_is_f32, double* partial,
+                              int nblk, double* out) {
+  const dim3 grd((unsigned)nblk, (unsigned)K);
   if (q_is_f32)
-    hipLaunchKernelGGL((k_field_reduce<32, float>), dim3(nblk), dim3(kReduceThreads), 0, L.stream,
-                       static_cast<const float*>(Q), N, K, mode, rest, partial);
+    hipLaunchKernelGGL((k_field_stats<float>), grd, dim3(kReduceThreads), 0, L.stream, static_cast<const float*>(Q),
+                       (unsigned)N, partial);
   else
-    hipLaunchKernelGGL((k_field_reduce<32, double>), dim3(nblk), dim3(kReduceThreads), 0, L.stream,
-                       static_cast<const double*>(Q), N, K, mode, rest, partial);
+    hipLaunchKernelGGL((k_field_stats<double>), grd, dim3(kReduceThreads), 0, L.stream, static_cast<const double*>(Q),
+                       (unsigned)N, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_reduce(L, K, partial, nblk, mode == 0 ? 0u : 0xffffffffu, out);
-}
-
-hipError_t launch_to_f32(hipStream_t s, const double* in, float* out, long long n) {
-  hipLaunchKernelGGL(k_to_f32, dim3(1024), dim3(256), 0, s, in, out, n);
-  return hipGetLastError();
+  MaxMask m;
+  for (int k = 0; k < K; ++k) m.add(3 * k + 1), m.add(3 * k + 2);
+  return launch_reduce(L, 3 * K, partial, nblk, m, out);
 }
 
 hipError_t launch_copy(hipStream_t s, void* dst, const void* src, size_t bytes) {

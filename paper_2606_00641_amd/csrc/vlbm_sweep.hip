@@ -938,6 +938,8 @@ inline dim3 flat_grid(const Launch& L, const Grid& g, int cells_per_lane) {
   return dim3((unsigned)((n + per - 1) / per));
 }
 
+dim3 cell_grid(const Grid& g, int bx) { return dim3((g.nx + bx - 1) / bx, g.ny, g.nz); }
+
 // One k_sweep launch with the template flags chosen at run time: parity, collision
 // (BGK or two-rate), lane exchange, x faces.  Only the combinations a caller can ask
 // for are instantiated.
