@@ -401,32 +401,49 @@ __global__ __launch_bounds__(kConvThreads, NZT == 1 ? 4 : 2) void k_conv(
     } else if (done) {
       load_zprev(jo, zp);
     }
-    if constexpr (CIN == 32) {
+    // the products of the taps kz in [k0, k1)
+    auto products = [&](auto k0c, auto k1c) __attribute__((always_inline)) {
+      constexpr int k0 = decltype(k0c)::value, k1 = decltype(k1c)::value;
+      if constexpr (CIN == 32) {
 #pragma unroll
-      for (int r = 0; r < MR + 2; ++r)
+        for (int r = 0; r < MR + 2; ++r)
 #pragma unroll
-        for (int dx = 0; dx < 3; ++dx) {
-          const bf16x8 a = *reinterpret_cast<const bf16x8*>(tz + ((py0 + r) * HALO + px + dx) * CIN + 8 * g);
+          for (int dx = 0; dx < 3; ++dx) {
+            const bf16x8 a = *reinterpret_cast<const bf16x8*>(tz + ((py0 + r) * HALO + px + dx) * CIN + 8 * g);
 #pragma unroll
-          for (int dy = 0; dy < 3; ++dy) {
-            const int m = r - dy;
-            if (m < 0 || m >= MR) continue;
+            for (int dy = 0; dy < 3; ++dy) {
+              const int m = r - dy;
+              if (m < 0 || m >= MR) continue;
 #pragma unroll
-            for (int kz = 0; kz < NZT; ++kz)
-              acc[kz][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[kz][3 * dy + dx], a, acc[kz][m], 0, 0, 0);
+              for (int kz = k0; kz < k1; ++kz)
+                acc[kz][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[kz][3 * dy + dx], a, acc[kz][m], 0, 0, 0);
+            }
           }
-        }
-    } else {
+      } else {
 #pragma unroll
-      for (int s = 0; s < KS; ++s)
+        for (int s = 0; s < KS; ++s)
 #pragma unroll
-        for (int m = 0; m < MR; ++m) {
-          bf16x8 a = *reinterpret_cast<const bf16x8*>(tz + ((py0 + m) * HALO + px) * CIN + tapoff[s]);
-          if (4 * s + 3 > 8 && 4 * s + g > 8) a = bf16x8{};  // zero padding of K
+          for (int m = 0; m < MR; ++m) {
+            bf16x8 a = *reinterpret_cast<const bf16x8*>(tz + ((py0 + m) * HALO + px) * CIN + tapoff[s]);
+            if (4 * s + 3 > 8 && 4 * s + g > 8) a = bf16x8{};  // zero padding of K
 #pragma unroll
-          for (int kz = 0; kz < NZT; ++kz)
-            acc[kz][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[kz][s], a, acc[kz][m], 0, 0, 0);
-        }
+            for (int kz = k0; kz < k1; ++kz)
+              acc[kz][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[kz][s], a, acc[kz][m], 0, 0, 0);
+          }
+      }
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
+    if constexpr (NZT == 1) {
+      products(I0{}, I1{});
+    } else if (j >= 2 && j + 3 <= np) {
+      products(I0{}, I3{});
+    } else {  // a plane at the end of the share: only the taps of output planes in it
+      if (j + 3 <= np) products(I0{}, I1{});
+      if (j >= 1 && j + 2 <= np) products(I1{}, I2{});
+      if (j >= 2) products(I2{}, I3{});
     }
     if constexpr (kTurns) {
 #pragma unroll
