@@ -194,7 +194,9 @@ vlbm_status vlbm_params_default(vlbm_params* p);
 vlbm_status vlbm_population_bytes(const vlbm_params* p, size_t* bytes);
 
 /* Create a context: validate p, allocate (or adopt) the population buffer and the
- * small FP64 reduction buffers.  No kernel runs.  *out is NULL on error. */
+ * small FP64 reduction buffers.  2D lattices in FP64/FP32 storage from 512^2 cells on also
+ * take a second population buffer (up to 4.5 GiB; without it, or if it cannot be had, every
+ * step sweeps in place).  No kernel runs.  *out is NULL on error. */
 vlbm_status vlbm_create(const vlbm_params* p, vlbm_ctx** out);
 
 /* f := f^eq(Q) in every cell (natural layout), step counter := 0.  Q is SoA
@@ -205,7 +207,10 @@ vlbm_status vlbm_init_fields(vlbm_ctx* c, const void* Q, int q_on_device, int q_
 
 /* Advance n >= 0 steps: per cell, gather the populations (in-place AA pattern),
  * moments, equation of state, fluxes, div B estimate, Powell source, BGK with
- * direct injection, scatter (Sec. 2.2-2.3).  Asynchronous on the context stream. */
+ * direct injection, scatter (Sec. 2.2-2.3).  Asynchronous on the context stream.  Where the
+ * context has a second population buffer, groups of 8 and 4 steps from an even step on run
+ * as passes of several steps each, to that buffer and back: the same arithmetic per cell,
+ * rounded as the compiler contracts it there. */
 vlbm_status vlbm_step(vlbm_ctx* c, int32_t n);
 
 /* Moments of the current populations: Q_out SoA [K][nz][ny][nx] (FP64 or FP32,

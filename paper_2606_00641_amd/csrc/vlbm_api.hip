@@ -69,6 +69,10 @@ long long plane_stride(long long N, int esize) {
   return bytes / esize;
 }
 
+// The multi-step passes of 2D lattices need a second population buffer; it is taken up to
+// this size (1.6 % of the card; 4096^2 cells of 13 variables in FP32).
+constexpr size_t kRowsBytes = (size_t)9 << 29;
+
 vlbm_status validate(const vlbm_params* p) {
   if (!p) return fail(nullptr, VLBM_ERR_ARG, "params is NULL");
   if (p->struct_size != sizeof(vlbm_params))
@@ -498,6 +502,14 @@ vlbm_status vlbm_create(const vlbm_params* p, vlbm_ctx** out) {
   c->L.block_x = p->block_x ? p->block_x : (p->nx >= 256 ? 256 : (p->nx >= 128 ? 128 : 64));
   c->L.block_flat = p->block_x ? p->block_x : (c->N < 256 * 256 ? 64 : 256);
   c->L.stream = c->stream;
+  // the multi-step passes' second buffer, on lattices they gain on; without it every step
+  // sweeps in place
+  if (c->pop_bytes <= kRowsBytes) c->levels = rows_levels(c->L, c->g, c->ph);
+  if (c->levels && hipMalloc(&c->d_alt, c->pop_bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    c->d_alt = nullptr;
+    c->levels = 0;
+  }
   *out = c;
   return VLBM_OK;
 }
@@ -574,9 +586,24 @@ vlbm_status vlbm_step(vlbm_ctx* c, int32_t n) {
   if (!c) return VLBM_ERR_ARG;
   if (n < 0) return fail(c, VLBM_ERR_ARG, "n = %d < 0", n);
   if (!c->initialized) return fail(c, VLBM_ERR_STATE, "vlbm_step before vlbm_init_fields");
-  for (int32_t j = 0; j < n; ++j) {
+  int32_t left = n;
+  while (left > 0) {
+    // two passes of t steps each, to the second buffer and back, from an even step on
+    int t = c->step & 1 ? 0 : c->levels;
+    if (t > 2 && left < 2 * t) t = 2;
+    if (t && left >= 2 * t) {
+      Grid there = c->g;
+      there.f = c->d_alt;
+      hipError_t e = launch_rows(c->L, c->g, c->d_alt, c->ph, t);
+      if (e == hipSuccess) e = launch_rows(c->L, there, c->f, c->ph, t);
+      if (e != hipSuccess) return hip_fail(c, e, "multi-step launch");
+      c->step += 2 * t;
+      left -= 2 * t;
+      continue;
+    }
     const vlbm_status s = vlbm_step_one(c);
     if (s != VLBM_OK) return s;
+    --left;
   }
   return VLBM_OK;
 }
@@ -795,6 +822,7 @@ void vlbm_destroy(vlbm_ctx* c) {
   if (c->d_partial2) (void)hipFree(c->d_partial2);
   if (c->d_totals) (void)hipFree(c->d_totals);
   if (c->d_Q) (void)hipFree(c->d_Q);
+  if (c->d_alt) (void)hipFree(c->d_alt);
   if (c->d_mask) (void)hipFree(c->d_mask);
   if (c->d_sprev) (void)hipFree(c->d_sprev);
   delete c;

@@ -147,6 +147,33 @@ __device__ __forceinline__ void st_shifted(void* base, size_t plane_bytes, int p
   *(VLBM_GLOBAL T*)(plane_base(base, plane_bytes, plane) + off) = v;
 }
 
+// Lane shifts across the 64-lane wavefront (DPP wave_shr:1 / wave_shl:1):
+// lane_up(e, v) gives lane l the v of lane l - 1 and lane 0 its own e; lane_dn(e, v)
+// gives lane l the v of lane l + 1 and lane 63 its own e.  A lane that is inactive
+// at the shift is read as out of range (its neighbour gets e), so the shifts run with
+// every lane of the wavefront active.
+__device__ __forceinline__ unsigned up1(unsigned e, unsigned v) {
+  return __builtin_amdgcn_update_dpp((int)e, (int)v, 0x138, 0xf, 0xf, false);
+}
+__device__ __forceinline__ unsigned dn1(unsigned e, unsigned v) {
+  return __builtin_amdgcn_update_dpp((int)e, (int)v, 0x130, 0xf, 0xf, false);
+}
+template <bool UP, typename T>
+__device__ __forceinline__ T lane_shift(T e, T v) {
+  auto sh = [](unsigned ee, unsigned vv) { return UP ? up1(ee, vv) : dn1(ee, vv); };
+  if constexpr (sizeof(T) == 8) {
+    const unsigned long long ue = __builtin_bit_cast(unsigned long long, e);
+    const unsigned long long uv = __builtin_bit_cast(unsigned long long, v);
+    const unsigned long long r = (unsigned long long)sh((unsigned)ue, (unsigned)uv) |
+                                 ((unsigned long long)sh((unsigned)(ue >> 32), (unsigned)(uv >> 32)) << 32);
+    return __builtin_bit_cast(T, r);
+  } else if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, sh(__builtin_bit_cast(unsigned, e), __builtin_bit_cast(unsigned, v)));
+  } else {
+    return (T)sh((unsigned)e, (unsigned)v);
+  }
+}
+
 // Dipole field of the body at point q (cell coordinates) and time t.
 __device__ inline void dipole_at(const Body& b, const double (&q)[3], double t, double (&B)[3]) {
   double r[3];

@@ -83,6 +83,13 @@ struct Launch {
 hipError_t launch_sweep(const Launch& L, const Grid& g, const Phys& ph, const Codec& cd, int parity,
                         const Inflow& in);
 
+// Several steps of a 2D periodic lattice in one pass, from g.f to the buffer `out` (same
+// layout, natural before and after; FP64 or FP32 storage, the direct source):
+// rows_levels, the most steps a pass takes here (0: none, else 2 or 4; 2 is always
+// possible too); launch_rows, one pass of `levels` steps.
+int rows_levels(const Launch& L, const Grid& g, const Phys& ph);
+hipError_t launch_rows(const Launch& L, const Grid& g, void* out, const Phys& ph, int levels);
+
 // Static faces (D3Q7 ideal model): every node of a non-periodic face takes
 // f := f^eq(Q_bc) at the given parity, Q_bc the inflow state on inflow faces, else
 // the moments of the nearest cell that lies on no non-periodic face.

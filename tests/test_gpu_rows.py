@@ -1,0 +1,72 @@
+"""Several steps of a 2D lattice in one pass over memory: against the same number of single
+steps, which sweep in place, and against the oracle.  Lattices one strip and one row past
+the passes' tilings, narrower than a strip, flatter than the rows a pass adds, batches."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from fieldcheck import rel_l2
+from test_gpu_parity import _euler, gpu_params, oracle_params, vb  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(model, shape):
+    nx, ny, nb = shape
+    if model == "resistive_2d":
+        w = synth.workload_resistive_2d(n=nx, ny=ny)
+        Q0 = np.concatenate([synth.resistive_2d_state((ny, nx), seed=3 + b, tau_M=w["tau_M"], tau_H=w["tau_H"],
+                                                      mu=w["mu"]) for b in range(nb)], axis=1)
+    elif model == "navier_cauchy":
+        w = synth.workload_elastic(dim=2, shape=shape)
+        Q0 = np.concatenate([synth.elastic_state((nx, ny, 1), seed=3 + b) for b in range(nb)], axis=1)
+    else:
+        w = synth.workload_fourier_2d()
+        rng = np.random.default_rng(5)
+        u = 0.05 * rng.standard_normal((3, nb, ny, nx))
+        B = 0.1 + 0.05 * rng.standard_normal((3, nb, ny, nx))
+        Q0 = synth.conserved_from_primitive(1.0 + 0.05 * rng.standard_normal((nb, ny, nx)), u, 0.6, B, 5.0 / 3.0)
+        if model == "euler":
+            w, Q0 = _euler(w), synth.without_field(Q0)
+    w["shape"] = shape
+    return w, np.ascontiguousarray(Q0)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+@pytest.mark.parametrize("model,shape", [("ideal", (601, 450, 1)), ("ideal", (100, 2700, 1)), ("ideal", (140000, 2, 1)),
+                                         ("ideal", (232, 130, 9)), ("euler", (583, 451, 1)),
+                                         ("navier_cauchy", (583, 451, 1)), ("resistive_2d", (583, 451, 1))])
+def test_passes_equal_single_steps(vb, model, shape, storage):  # noqa: F811
+    """15 steps at once (in FP32 one pair of 4-step passes, one of 2-step passes and three
+    sweeps) and one by one.  Both within the parity gate of the oracle: FP64 1e-10; FP32
+    1e-5, or for the small transported fields, whose FP32 rounding exceeds it, twice the
+    single steps' own distance (the same arithmetic per cell, rounded differently), and
+    then no further from one another than the two distances together."""
+    w, Q0 = _case(model, shape)
+    K = Q0.shape[0]
+    print("case passes", model, shape, storage, flush=True)
+    sims = [vb.Vlbm(gpu_params(vb, w, storage)) for _ in range(2)]
+    for sim in sims:
+        sim.vlbm_init_fields(Q0)
+    sims[0].vlbm_step(15)
+    for _ in range(15):
+        sims[1].vlbm_step(1)
+    assert sims[0].vlbm_get_step() == sims[1].vlbm_get_step() == 15
+    Qa, Qb = (sim.vlbm_moments()[0] for sim in sims)
+    op = oracle_params(w)
+    f = oracle.init(op, Q0)
+    oracle.run(op, f, 15)
+    Qo = oracle.moments(op, f)[0]
+    gate = 1e-10 if storage == "f64" else 1e-5
+    own, far, apart = rel_l2(Qb, Qo, K), rel_l2(Qa, Qo, K), rel_l2(Qa, Qb, K)
+    for name in own:
+        assert far[name] <= max(gate, 2.0 * own[name]), (name, far[name], own[name])
+        assert apart[name] <= max(gate, 3.0 * own[name]), (name, apart[name], own[name])
+    # populations of single cells after more passes from an odd step on (natural layout)
+    sims[0].vlbm_step(9)
+    for _ in range(9):
+        sims[1].vlbm_step(1)
+    cells = np.array([0, 1, shape[0] - 1, shape[0], 57, 58, 63, shape[0] * shape[1] - 1])
+    a, b = (sim.vlbm_gather_cells(cells) for sim in sims)
+    assert np.abs(a - b).max() <= gate * np.abs(b).max()
