@@ -904,7 +904,9 @@ inline bool flat_rows(const Launch& L, const Grid& g) {
   return true;
 }
 // Two cells per lane from this many cells on (256 workgroups of 512 cells, one per CU):
-// on a 76 x 78 lattice, 12 workgroups, they took 16.6 us a step against 14.4 us.
+// on a 76 x 78 lattice, 12 workgroups, they took 16.6 us a step against 14.4 us.  D3Q7 only:
+// on D2Q5 the compiler contracts the pair form's arithmetic differently from the one-cell
+// sweep these lattices took before, which moves the 16-bit rounding of single populations.
 constexpr long long kFlatPairCells = 256 * 512;
 inline dim3 flat_grid(const Launch& L, const Grid& g, int cells_per_lane) {
   const long long per = (long long)L.block_flat * cells_per_lane, n = (long long)g.nx * g.ny * g.nz;
@@ -1044,7 +1046,7 @@ hipError_t sweep_t(const Launch& L, const Grid& g, const Phys& ph, const Codec& 
   if constexpr ((ST == ST_F16 || ST == ST_BF16) && MODEL != 1 && MODEL != 4) {
     if (const int bw = pair_width(g, L.block_x, D == 3 && MODEL == 0))
       return sweep2_t<ST, D, MODEL>(L, g, ph, cd, parity, bw, Body{}, in);
-    if (flat_rows(L, g) && (parity == 0 || g.nx % 2 == 0) && (long long)g.nx * g.ny * g.nz >= kFlatPairCells) {
+    if (D == 3 && flat_rows(L, g) && (parity == 0 || g.nx % 2 == 0) && (long long)g.nx * g.ny * g.nz >= kFlatPairCells) {
       auto go = [&](auto par_c, auto coll_c) {
         hipLaunchKernelGGL((k_sweep2<ST, D, MODEL, decltype(par_c)::value, decltype(coll_c)::value, false, false, true>),
                            flat_grid(L, g, 2), dim3(L.block_flat), 0, L.stream, g, ph, cd, Body{}, in);
