@@ -69,7 +69,7 @@ long long plane_stride(long long N, int esize) {
   return bytes / esize;
 }
 
-// The multi-step passes of 2D lattices need a second population buffer; it is taken up to
+// The multi-step passes need a second population buffer; it is taken up to
 // this size (1.6 % of the card; 4096^2 cells of 13 variables in FP32).
 constexpr size_t kRowsBytes = (size_t)9 << 29;
 
@@ -504,7 +504,7 @@ vlbm_status vlbm_create(const vlbm_params* p, vlbm_ctx** out) {
   c->L.stream = c->stream;
   // the multi-step passes' second buffer, on lattices they gain on; without it every step
   // sweeps in place
-  if (c->pop_bytes <= kRowsBytes) c->levels = rows_levels(c->L, c->g, c->ph);
+  if (c->pop_bytes <= kRowsBytes && !c->has_faces && !p->body) c->levels = rows_levels(c->L, c->g, c->ph);
   if (c->levels && hipMalloc(&c->d_alt, c->pop_bytes) != hipSuccess) {
     (void)hipGetLastError();
     c->d_alt = nullptr;

@@ -83,8 +83,9 @@ struct Launch {
 hipError_t launch_sweep(const Launch& L, const Grid& g, const Phys& ph, const Codec& cd, int parity,
                         const Inflow& in);
 
-// Several steps of a 2D periodic lattice in one pass, from g.f to the buffer `out` (same
-// layout, natural before and after; FP64 or FP32 storage, the direct source):
+// Several steps of a periodic lattice without a body in one pass, from g.f to the buffer
+// `out` (same layout, natural before and after; FP64 or FP32 storage in 2D, FP32 in 3D, the
+// direct source):
 // rows_levels, the most steps a pass takes here (0: none, else 2 or 4; 2 is always
 // possible too); launch_rows, one pass of `levels` steps.
 int rows_levels(const Launch& L, const Grid& g, const Phys& ph);

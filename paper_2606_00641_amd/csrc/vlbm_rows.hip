@@ -1,4 +1,5 @@
-// Several steps of a 2D periodic lattice in one pass over memory (gfx950).
+// Several steps of a periodic lattice in one pass over memory (gfx950): 2D (k_rows), and
+// below it 3D (k_cols).
 //
 // The sweep (vlbm_sweep.hip) reads and writes every population once per step and is bound
 // by that traffic.  Here a wavefront walks up a strip of 64 x columns and carries T time
@@ -154,10 +155,162 @@ int rows_for(const Grid& g, int T) {
   return (int)std::min<long long>(g.ny, std::max<long long>(8, (g.ny + per - 1) / per));
 }
 
+// Two steps of a 3D lattice in one pass: a workgroup of eight wavefronts holds eight x rows,
+// consecutive in y, of a strip of up to 62 columns and the one on each side of it, and walks
+// up in z.  Level 1 collides plane z in all eight rows; along x it streams between lanes,
+// along y through LDS, along z over the lane's own planes; level 2 collides plane z - 1 of
+// the next step in the inner six rows.  The strip's columns of these rows are whole; a
+// workgroup stages two planes more than it completes.  The exchange has two LDS buffers, so
+// that one barrier per plane is enough: a plane's is written again only after the next
+// plane's barrier, which every reader has passed by then.
+// Bound by the memory path of one workgroup per CU (256 VGPRs): a wavefront's loads and
+// stores of a plane, 56 each, pass one after the other; without its collisions the kernel
+// takes as long.  The next plane is therefore asked for after level 1's collision, during
+// which the stores of the plane before drain (120^3 110 -> 103 us a step), and the columns
+// are shared evenly among as few strips as hold them (190^3 570 -> 420 us: four strips of 48
+// columns instead of three of 62 and one of 4), in multiples of eight, whole 32-byte sectors.
+// Per step, the in-place sweep against passes, 8 variables: 64^3 23.7 -> 20.3 us, 160^3
+// 361 -> 241, 190^3 663 -> 420, 256^3 1340 -> 1204; 5 variables 90^3 38.5 -> 24.5, 210^3 566
+// -> 374; 9 variables 110^3 137 -> 117, 230^3 1378 -> 958.  A tile of any width with both
+// exchanges through LDS, and strips that run on over the rows' ends, fill the lanes better
+// but need per-lane row addresses and spill: 190^3 474 and 698 us, 240^3 1010 and 1263
+// against 873.  Twelve wavefronts in 168 VGPRs spill more (160^3 415 us).
+constexpr int kColWaves = 8, kColRows = kColWaves - 2, kColV = 62;
+template <int MODEL, int COLL>
+__global__ __launch_bounds__(64 * kColWaves, 2) void k_cols(const Grid g, void* const out, const Phys ph, int V, int planes) {
+  using R = float;
+  constexpr int NQ = 7, K = kNVars<MODEL>;
+  constexpr unsigned ES = sizeof(R);
+  __shared__ R xch[2][kColWaves][2][K][64];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int nx = g.nx, ny = g.ny, nz = g.nz;
+  const int strips = (nx + V - 1) / V, tiles = (ny + kColRows - 1) / kColRows;
+  const unsigned nb = gridDim.x, L = blockIdx.x, q = nb / 8, rem = nb % 8, xcd = L % 8;
+  const int task = (int)(xcd * q + min(xcd, rem) + L / 8);
+  const int s = task % strips, yt = (task / strips) % tiles, ch = task / (strips * tiles);
+  const int z0 = ch * planes, nj = min(planes, nz - z0) + 2;
+  // lanes past the strip's last neighbour read that one's address again, not memory of their own
+  int x = (s * V - 1 + min(lane, nx - s * V + 1)) % nx;
+  x = x < 0 ? x + nx : x;
+  const int yi = yt * kColRows + wv - 1;  // this wavefront's row
+  const int y = (yi % ny + ny) % ny;
+  const bool inner = wv >= 1 && wv <= kColRows && yi < ny;
+  const bool mine = inner && lane >= 1 && lane <= V && lane - 1 < nx - s * V;
+  const unsigned pl = (unsigned)nx * (unsigned)ny;
+  const unsigned xo = (unsigned)x, xp = x + 1 == nx ? 0u : xo + 1u, xm = x == 0 ? (unsigned)nx - 1u : xo - 1u;
+  const unsigned ro = (unsigned)y * (unsigned)nx;
+  const unsigned rp = (unsigned)(y + 1 == ny ? 0 : y + 1) * (unsigned)nx, rm = (unsigned)(y == 0 ? ny - 1 : y - 1) * (unsigned)nx;
+  const size_t pb = (size_t)g.stride * ES;
+  void* const F = g.f;
+
+  R f[K][NQ], nf[K][NQ];
+  // the plane below the one in flight after level 1: f_0, f_{+-x}, f_{+-y}, f_{+z} as they
+  // arrive in it, and the f_{+z} it sends up
+  R C[K][7];
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+#pragma unroll
+    for (int i = 0; i < 7; ++i) C[k][i] = R(0);
+  auto load = [&](R (&d)[K][NQ], int z) __attribute__((always_inline)) {
+    const unsigned off = ((unsigned)z * pl + ro + xo) * ES;
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+      for (int i = 0; i < NQ; ++i) d[k][i] = get<R>(F, pb, k * NQ + i, off);
+  };
+  int zr = z0 == 0 ? nz - 1 : z0 - 1, zw = z0;
+  load(f, zr);
+#pragma unroll 1
+  for (int j = 0; j < nj; ++j) {
+    zr = zr + 1 == nz ? 0 : zr + 1;
+    R dl;
+    collide<R, 3, MODEL, COLL>(f, ph, dl);
+    if (j + 1 < nj) load(nf, zr);
+    auto& e = xch[j & 1];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      e[wv][0][k][lane] = f[k][3];
+      e[wv][1][k][lane] = f[k][4];
+    }
+    __syncthreads();
+    R h[K][NQ];
+    const int below = wv == 0 ? 0 : wv - 1, above = wv == kColWaves - 1 ? wv : wv + 1;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+#pragma unroll
+      for (int i = 0; i < 6; ++i) h[k][i] = C[k][i];
+      h[k][6] = f[k][6];
+      C[k][0] = f[k][0];
+      C[k][1] = from_left(f[k][1]);
+      C[k][2] = from_right(f[k][2]);
+      C[k][3] = e[below][0][k][lane];
+      C[k][4] = e[above][1][k][lane];
+      C[k][5] = C[k][6];
+      C[k][6] = f[k][5];
+    }
+    if (j >= 2) {
+      if (inner) {
+        collide<R, 3, MODEL, COLL>(h, ph, dl);
+        const unsigned zo = (unsigned)zw * pl, zp = (unsigned)(zw + 1 == nz ? 0 : zw + 1) * pl,
+                       zm = (unsigned)(zw == 0 ? nz - 1 : zw - 1) * pl;
+        const unsigned dst[NQ] = {(zo + ro + xo) * ES, (zo + ro + xp) * ES, (zo + ro + xm) * ES, (zo + rp + xo) * ES,
+                                  (zo + rm + xo) * ES, (zp + ro + xo) * ES, (zm + ro + xo) * ES};
+        if (mine) {
+#pragma unroll
+          for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) st_shifted<R>(out, pb, k * NQ + i, dst[i], h[k][i]);
+        }
+      }
+      ++zw;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+      for (int i = 0; i < NQ; ++i) f[k][i] = nf[k][i];
+  }
+}
+
+template <int MODEL>
+hipError_t cols_t(const Launch& L, const Grid& g, void* out, const Phys& ph) {
+  const int strips = (g.nx + kColV - 1) / kColV, V = std::min(kColV, ((g.nx + strips - 1) / strips + 7) / 8 * 8);
+  const long long cols = (long long)((g.nx + V - 1) / V) * ((g.ny + kColRows - 1) / kColRows);
+  // planes per workgroup: the share of z for which the rounds of workgroups over 256 CUs
+  // times a workgroup's planes, the two it stages beyond them and its start is least
+  long long best = -1;
+  int planes = g.nz;
+  for (int n = 1; n <= g.nz && n <= 256; ++n) {
+    const int p = (g.nz + n - 1) / n;
+    const long long cost = (cols * ((g.nz + p - 1) / p) + 255) / 256 * (p + 3);
+    if (best < 0 || cost < best) best = cost, planes = p;
+  }
+  const dim3 grd((unsigned)(cols * ((g.nz + planes - 1) / planes))), blk(64 * kColWaves);
+  if (ph.collision)
+    hipLaunchKernelGGL((k_cols<MODEL, 1>), grd, blk, 0, L.stream, g, out, ph, V, planes);
+  else
+    hipLaunchKernelGGL((k_cols<MODEL, 0>), grd, blk, 0, L.stream, g, out, ph, V, planes);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 int rows_levels(const Launch& L, const Grid& g, const Phys& ph) {
-  if (L.dim != 2 || (L.storage != ST_F32 && L.storage != ST_F64) || ph.source != 0 || g.mask) return 0;
+  if ((L.storage != ST_F32 && L.storage != ST_F64) || ph.source != 0 || g.mask) return 0;
+  if (L.dim == 3) {
+    if (L.storage != ST_F32 || L.model == 1) return 0;
+    // From 2^18 cells on (48^3 stays in the caches: 9.4 us a step against 11.6), with planes,
+    // rows and columns enough for the two planes, two of eight rows and two columns a tile
+    // reads beyond its own (200^2 x 4 14.7 us against 15.9, 200 x 7 x 200 25.1 against 23.4,
+    // 32 x 200^2 105 against 109), where the last of three and more strips is not nearly empty (130^3, 5
+    // variables, 108 us against 114).  With 9 variables, more of whose registers spill, only
+    // where the strips are three quarters full and the in-place rows not all aligned lines
+    // (90^3 67.5 us against 68.8, 256^2 x 128 742 against 806).
+    const int strips = (g.nx + kColV - 1) / kColV, tiles = (g.ny + kColRows - 1) / kColRows;
+    const double fill = (double)g.nx / (strips * kColV);
+    if ((long long)g.nx * g.ny * g.nz < 1 << 18 || g.nx < 56 || g.nz < 48 || 4 * g.ny < 3 * tiles * kColRows) return 0;
+    if ((strips > 2 && fill < 0.71) || (L.model == 3 && (fill < 0.75 || g.nx % 64 == 0))) return 0;
+    return 2;
+  }
   if (L.storage == ST_F64 && L.model == 4) return 0;  // its levels do not fit the registers
   const int T = L.storage == ST_F64 || L.model == 4 ? 2 : 4;
   // from 512^2 on (below, the populations sit in the L2s and the sweep is faster: 384^2 FP32
@@ -168,6 +321,14 @@ int rows_levels(const Launch& L, const Grid& g, const Phys& ph) {
 }
 
 hipError_t launch_rows(const Launch& L, const Grid& g, void* out, const Phys& ph, int levels) {
+  if (L.dim == 3) {
+    switch (L.model) {
+      case 0: return cols_t<0>(L, g, out, ph);
+      case 2: return cols_t<2>(L, g, out, ph);
+      case 3: return cols_t<3>(L, g, out, ph);
+      default: return hipErrorInvalidValue;
+    }
+  }
   const int rows = rows_for(g, levels);
 #define ROWS_CASE(S, M, T) \
   if (L.storage == S && L.model == M && levels == T) return rows_t<S, M, T>(L, g, out, ph, rows);

@@ -1,4 +1,4 @@
-"""Several steps of a 2D lattice in one pass over memory: against the same number of single
+"""Several steps of a lattice in one pass over memory: against the same number of single
 steps, which sweep in place, and against the oracle.  Lattices one strip and one row past
 the passes' tilings, narrower than a strip, flatter than the rows a pass adds, batches."""
 import numpy as np
@@ -7,7 +7,7 @@ import pytest
 import oracle
 import synth
 from fieldcheck import rel_l2
-from test_gpu_parity import _euler, gpu_params, oracle_params, vb  # noqa: F401
+from test_gpu_parity import _euler, boosted, gpu_params, oracle_params, vb  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -70,3 +70,52 @@ def test_passes_equal_single_steps(vb, model, shape, storage):  # noqa: F811
     cells = np.array([0, 1, shape[0] - 1, shape[0], 57, 58, 63, shape[0] * shape[1] - 1])
     a, b = (sim.vlbm_gather_cells(cells) for sim in sims)
     assert np.abs(a - b).max() <= gate * np.abs(b).max()
+
+
+# 3D passes: one strip, exactly full and narrowest; two strips one column past one; four of 48
+# columns and a part; rows and planes that leave the last tile and share part empty
+@pytest.mark.parametrize("collision", ["bgk", "trt"])
+@pytest.mark.parametrize("model,shape", [("ideal", (62, 65, 66)), ("ideal", (63, 89, 48)), ("ideal", (190, 29, 49)),
+                                         ("ideal", (56, 17, 276)), ("euler", (119, 47, 49)),
+                                         ("navier_cauchy", (119, 47, 49))])
+def test_passes_equal_single_steps_3d(vb, model, shape, collision):  # noqa: F811
+    """15 steps at once (three pairs of 2-step passes and three sweeps) and one by one, FP32;
+    the gates of the 2D test, and the populations after more passes from an odd step on."""
+    if model == "navier_cauchy":
+        w = synth.workload_elastic(dim=3, shape=shape)
+        Q0 = synth.elastic_state(shape, seed=3)
+    else:
+        w = synth.workload_slab_3d()
+        w["shape"] = shape
+        Q0 = np.ascontiguousarray(boosted(synth.planar_discontinuity_3d(seed=5, shape=shape[::-1])[0], (0.3, -0.2, 0.25)))
+        if model == "euler":
+            w, Q0 = _euler(w), synth.without_field(Q0)
+    K = Q0.shape[0]
+    print("case passes 3d", model, shape, collision, flush=True)
+    p = gpu_params(vb, w, "f32")
+    op = oracle_params(w)
+    if collision == "trt":
+        p.collision, p.trt_magic = 1, 0.25
+        op.collision, op.trt_magic = 1, 0.25
+    sims = [vb.Vlbm(p) for _ in range(2)]
+    for sim in sims:
+        sim.vlbm_init_fields(Q0)
+    sims[0].vlbm_step(15)
+    for _ in range(15):
+        sims[1].vlbm_step(1)
+    assert sims[0].vlbm_get_step() == sims[1].vlbm_get_step() == 15
+    Qa, Qb = (sim.vlbm_moments()[0] for sim in sims)
+    f = oracle.init(op, Q0)
+    oracle.run(op, f, 15)
+    Qo = oracle.moments(op, f)[0]
+    own, far, apart = rel_l2(Qb, Qo, K), rel_l2(Qa, Qo, K), rel_l2(Qa, Qb, K)
+    for name in own:
+        assert far[name] <= max(1e-5, 2.0 * own[name]), (name, far[name], own[name])
+        assert apart[name] <= max(1e-5, 3.0 * own[name]), (name, apart[name], own[name])
+    sims[0].vlbm_step(9)
+    for _ in range(9):
+        sims[1].vlbm_step(1)
+    n = int(np.prod(shape))
+    cells = np.unique(np.concatenate([[0, shape[0] - 1, shape[0], n - 1], np.random.default_rng(1).integers(0, n, 4000)]))
+    a, b = (sim.vlbm_gather_cells(cells) for sim in sims)
+    assert np.abs(a - b).max() <= 1e-5 * np.abs(b).max()
