@@ -194,9 +194,9 @@ vlbm_status vlbm_params_default(vlbm_params* p);
 vlbm_status vlbm_population_bytes(const vlbm_params* p, size_t* bytes);
 
 /* Create a context: validate p, allocate (or adopt) the population buffer and the
- * small FP64 reduction buffers.  2D lattices in FP64/FP32 storage from 512^2 cells on, and
- * periodic 3D lattices in FP32 storage of up to 9 variables from 2^18 cells on, also take a
- * second population buffer (up to 4.5 GiB; without it, or if it cannot be had, every step
+ * small FP64 reduction buffers.  Most 2D lattices in FP64/FP32 storage, and periodic 3D
+ * lattices in FP32 storage of up to 9 variables from 2^18 cells on, also take a second
+ * population buffer (up to 4.5 GiB; without it, or if it cannot be had, every step
  * sweeps in place).  No kernel runs.  *out is NULL on error. */
 vlbm_status vlbm_create(const vlbm_params* p, vlbm_ctx** out);
 

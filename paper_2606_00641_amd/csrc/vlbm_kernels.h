@@ -86,8 +86,7 @@ hipError_t launch_sweep(const Launch& L, const Grid& g, const Phys& ph, const Co
 // Several steps of a periodic lattice without a body in one pass, from g.f to the buffer
 // `out` (same layout, natural before and after; FP64 or FP32 storage in 2D, FP32 in 3D, the
 // direct source):
-// rows_levels, the most steps a pass takes here (0: none, else 2 or 4; 2 is always
-// possible too); launch_rows, one pass of `levels` steps.
+// rows_levels, the most steps a pass takes here (0: none, 2, or 4 or 2); launch_rows, one pass of `levels` steps.
 int rows_levels(const Launch& L, const Grid& g, const Phys& ph);
 hipError_t launch_rows(const Launch& L, const Grid& g, void* out, const Phys& ph, int levels);
 

@@ -1,5 +1,5 @@
-// Several steps of a periodic lattice in one pass over memory (gfx950): 2D (k_rows), and
-// below it 3D (k_cols).
+// Several steps of a periodic lattice in one pass over memory (gfx950): large 2D lattices in
+// FP32 (k_rows, described here), other 2D lattices (k_tiles), 3D lattices in FP32 (k_cols).
 //
 // The sweep (vlbm_sweep.hip) reads and writes every population once per step and is bound
 // by that traffic.  Here a wavefront walks up a strip of 64 x columns and carries T time
@@ -18,8 +18,7 @@
 // Bound by one wavefront per SIMD working through its levels (293 VGPRs for 8 variables in
 // FP32 and 4 levels; held to 256 they spill, and a step took 105 us instead of 28 on
 // 1024^2).  Per step, the in-place sweep against passes: 8 variables FP32 1024^2 61.2 ->
-// 27.5 us, 2000^2 232 -> 82 us (4 levels; 3 levels at two wavefronts per SIMD 39 and 175);
-// FP64 1024^2 124 -> 87 us; 13 variables FP32 2000^2 405 -> 293 us (2 levels).
+// 27.5 us, 2000^2 232 -> 82 us (4 levels; 3 levels at two wavefronts per SIMD 39 and 175).
 #include "vlbm_device.h"
 
 namespace vlbm {
@@ -42,10 +41,9 @@ __device__ __forceinline__ R get(void* base, size_t plane_bytes, int plane, unsi
 // T levels, one wavefront per strip; workgroups are numbered so that each XCD gets
 // consecutive ones (neighbouring strips share the lines at their edges).  The next row's
 // populations are loaded while the levels of this one collide.
-template <int ST, int MODEL, int T, int COLL>
+template <int MODEL, int T, int COLL>
 __global__ __launch_bounds__(256) void k_rows(const Grid g, void* const out, const Phys ph, int rows) {
-  using R = typename Store<ST>::R;
-  static_assert(sizeof(R) == sizeof(typename Store<ST>::T), "FP64 or FP32 storage");
+  using R = float;
   constexpr int NQ = 5, K = kNVars<MODEL>, V = 64 - 2 * (T - 1);
   constexpr unsigned ES = sizeof(R);
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -134,18 +132,6 @@ __global__ __launch_bounds__(256) void k_rows(const Grid g, void* const out, con
   }
 }
 
-template <int ST, int MODEL, int T>
-hipError_t rows_t(const Launch& L, const Grid& g, void* out, const Phys& ph, int rows) {
-  constexpr int V = 64 - 2 * (T - 1);
-  const long long tasks = (long long)((g.nx + V - 1) / V) * ((g.ny + rows - 1) / rows) * g.nz;
-  const dim3 grd((unsigned)((tasks + 3) / 4)), blk(256);
-  if (ph.collision)
-    hipLaunchKernelGGL((k_rows<ST, MODEL, T, 1>), grd, blk, 0, L.stream, g, out, ph, rows);
-  else
-    hipLaunchKernelGGL((k_rows<ST, MODEL, T, 0>), grd, blk, 0, L.stream, g, out, ph, rows);
-  return hipGetLastError();
-}
-
 // Rows per strip: so many that the strips of the lattice fill the chip once, one wavefront
 // per SIMD (1024), and never a few of them a second time; at least 8 (a strip reads and
 // partly collides 2 (T - 1) rows more than it completes).
@@ -153,6 +139,120 @@ int rows_for(const Grid& g, int T) {
   const int V = 64 - 2 * (T - 1);
   const long long strips = (long long)((g.nx + V - 1) / V) * g.nz, per = std::max<long long>(1, 1024 / strips);
   return (int)std::min<long long>(g.ny, std::max<long long>(8, (g.ny + per - 1) / per));
+}
+
+template <int MODEL, int T>
+hipError_t rows_t(const Launch& L, const Grid& g, void* out, const Phys& ph) {
+  constexpr int V = 64 - 2 * (T - 1);
+  const int rows = rows_for(g, T);
+  const long long tasks = (long long)((g.nx + V - 1) / V) * ((g.ny + rows - 1) / rows) * g.nz;
+  const dim3 grd((unsigned)((tasks + 3) / 4)), blk(256);
+  if (ph.collision)
+    hipLaunchKernelGGL((k_rows<MODEL, T, 1>), grd, blk, 0, L.stream, g, out, ph, rows);
+  else
+    hipLaunchKernelGGL((k_rows<MODEL, T, 0>), grd, blk, 0, L.stream, g, out, ph, rows);
+  return hipGetLastError();
+}
+
+// T steps of a 2D lattice in one pass, one cell per thread: a tile of TX x TY cells, those
+// whose result is whole, (TX - 2 (T - 1)) x (TY - 2 (T - 1)), and T - 1 around them; between
+// the levels what moves passes through LDS.  For lattices on which k_rows' long strips leave
+// the chip idle, and in FP64, where k_rows' registers hold two levels only.
+// Bound on small lattices by the launch and the levels' latency (64^2: about 5 us a launch and
+// 1.2 us a level in FP64, 0.8 in FP32), on large ones by the overlap: 512 threads complete 260
+// cells, 256 threads 100.  Neighbouring tiles go to one XCD, whose L2 then holds what they
+// share (512^2 FP32 10.3 -> 7.1 us).  Per step, the in-place sweep against passes of 4: 8
+// variables FP64 64^2 4.6 -> 2.3 us, 256^2 8.0 -> 5.0, 1024^2 124 -> 70 (k_rows 86); FP32
+// 64^2 4.3 -> 1.8, 512^2 18 -> 7.1 (k_rows 12.3); 13 variables FP64 64^2 6.6 -> 3.5, 2000^2
+// 838 -> 649, FP32 256^2 9.0 -> 4.7, 2000^2 405 -> 267 (k_rows, 2 levels, 294).
+template <int ST, int MODEL, int T, int TX, int TY, int COLL>
+__global__ __launch_bounds__(TX* TY) void k_tiles(const Grid g, void* const out, const Phys ph) {
+  using R = typename Store<ST>::R;
+  constexpr int NQ = 5, K = kNVars<MODEL>, B = TX * TY, H = T - 1, IX = TX - 2 * H, IY = TY - 2 * H;
+  constexpr unsigned ES = sizeof(R);
+  __shared__ R e[4][K][B];
+  const int t = threadIdx.x, col = t % TX, row = t / TX;
+  const int nx = g.nx, ny = g.ny, nbx = (nx + IX - 1) / IX, nby = (ny + IY - 1) / IY;
+  const unsigned nb = gridDim.x, L = blockIdx.x, q = nb / 8, rem = nb % 8, xcd = L % 8;
+  const int task = (int)(xcd * q + min(xcd, rem) + L / 8);  // neighbouring tiles on one XCD
+  const int x0 = task % nbx * IX, y0 = task / nbx % nby * IY;
+  const bool mine = col >= H && col < TX - H && row >= H && row < TY - H && x0 + col - H < nx && y0 + row - H < ny;
+  int x = (x0 + col - H) % nx, y = (y0 + row - H) % ny;
+  x = x < 0 ? x + nx : x;
+  y = y < 0 ? y + ny : y;
+  const unsigned slice = (unsigned)(task / (nbx * nby)) * (unsigned)nx * (unsigned)ny;
+  auto at = [&](int xx, int yy) { return (slice + (unsigned)yy * (unsigned)nx + (unsigned)xx) * ES; };
+  const unsigned o = at(x, y);
+  const size_t pb = (size_t)g.stride * ES;
+  R f[K][NQ], dl;
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) f[k][i] = get<R>(g.f, pb, k * NQ + i, o);
+  const int tl = max(t - 1, 0), tr = min(t + 1, B - 1), td = max(t - TX, 0), tu = min(t + TX, B - 1);
+#pragma unroll
+  for (int lv = 0; lv < T; ++lv) {
+    collide<R, 2, MODEL, COLL>(f, ph, dl);
+    if (lv == T - 1) break;
+    if (lv) __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) e[d][k][t] = f[k][1 + d];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      f[k][1] = e[0][k][tl];
+      f[k][2] = e[1][k][tr];
+      f[k][3] = e[2][k][td];
+      f[k][4] = e[3][k][tu];
+    }
+  }
+  if (!mine) return;
+  const unsigned dst[NQ] = {o, at(x + 1 == nx ? 0 : x + 1, y), at(x == 0 ? nx - 1 : x - 1, y),
+                            at(x, y + 1 == ny ? 0 : y + 1), at(x, y == 0 ? ny - 1 : y - 1)};
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) st_shifted<R>(out, pb, k * NQ + i, dst[i], f[k][i]);
+}
+
+long long tiles_of(const Grid& g, int TX, int TY, int T) {
+  const int IX = TX - 2 * (T - 1), IY = TY - 2 * (T - 1);
+  return (long long)((g.nx + IX - 1) / IX) * ((g.ny + IY - 1) / IY) * g.nz;
+}
+
+template <int ST, int MODEL, int T, int TX, int TY>
+hipError_t tiles_s(const Launch& L, const Grid& g, void* out, const Phys& ph) {
+  const dim3 grd((unsigned)tiles_of(g, TX, TY, T)), blk(TX * TY);
+  if (ph.collision)
+    hipLaunchKernelGGL((k_tiles<ST, MODEL, T, TX, TY, 1>), grd, blk, 0, L.stream, g, out, ph);
+  else
+    hipLaunchKernelGGL((k_tiles<ST, MODEL, T, TX, TY, 0>), grd, blk, 0, L.stream, g, out, ph);
+  return hipGetLastError();
+}
+
+// The tiles' width, 16 or 32, or 0: no tiles.  32 x 16 tiles once there are cells enough that
+// the smaller overlap counts (8 variables FP32 100^2 x 4 3.2 us a step in 16 x 16 tiles, 3.0
+// in 32 x 16; FP64, 256^2 6.3 and 7.3, 384^2 12.2 and 11.9), where they are the fewer
+// threads (8 x 4000 2.7 and 3.8), and where their exchange fits the LDS (not 13 variables in
+// FP64).  No tiles where they fill the chip with overlap and empty lanes: 1400^2 FP32 in 16 x
+// 16 tiles, 2.6 threads a cell, 111 us a step like the sweep (32 x 16, 2.0: 49); FP64 158 in 16
+// x 16 against 234; 13 variables FP64 2 x 4000, 400 tiles, 6.7 against 5.8.
+int tile_width(const Launch& L, const Grid& g) {
+  const bool heavy = L.storage == ST_F64 || L.model == 4, fits = !(L.storage == ST_F64 && L.model == 4);
+  const long long N = (long long)g.nx * g.ny * g.nz, n16 = tiles_of(g, 16, 16, 4), n32 = tiles_of(g, 32, 16, 4);
+  const bool wide = fits && N > (heavy ? 1 << 16 : 1 << 14) && 2 * n32 < n16;
+  const long long threads = wide ? 512 * n32 : 256 * n16;
+  if (threads > (fits ? 1 << 17 : 1 << 16) && 10 * threads > (heavy ? 27 : 24) * N) return 0;
+  return wide ? 32 : 16;
+}
+
+template <int ST, int MODEL, int T>
+hipError_t tiles_t(const Launch& L, const Grid& g, void* out, const Phys& ph) {
+  if constexpr (!(ST == ST_F64 && MODEL == 4))
+    if (tile_width(L, g) == 32) return tiles_s<ST, MODEL, T, 32, 16>(L, g, out, ph);
+  return tiles_s<ST, MODEL, T, 16, 16>(L, g, out, ph);
 }
 
 // Two steps of a 3D lattice in one pass: a workgroup of eight wavefronts holds eight x rows,
@@ -292,6 +392,18 @@ hipError_t cols_t(const Launch& L, const Grid& g, void* out, const Phys& ph) {
   return hipGetLastError();
 }
 
+// 2D passes of 4 steps by rows (k_rows) instead of tiles: FP32, up to 9 variables, where the
+// populations exceed 190 MB and leave the last-level cache (8 variables 800^2 15.7 us a step
+// against 13.3, 1024^2 27.3 and 26.9, 1400^2 44.4 and 49.0, 2000^2 81.9 and 97.0; 9 variables
+// 1024^2 29.5 and 31.3; 5 variables 1024^2 14.1 and 11.3, 1400^2 28.3 and 29.2), and where the
+// strips waste at most a quarter of their lanes and are no flatter than the rows they add.
+bool by_rows(const Launch& L, const Grid& g) {
+  constexpr int V = 64 - 2 * 3;
+  const int K = L.model == 0 ? 8 : L.model == 2 ? 5 : 9, strips = (g.nx + V - 1) / V;
+  return L.storage == ST_F32 && L.model != 4 && (long long)g.nx * g.ny * g.nz * K >= 9 << 20 && g.ny >= 16 &&
+         4LL * g.nx >= 3LL * strips * V;
+}
+
 }  // namespace
 
 int rows_levels(const Launch& L, const Grid& g, const Phys& ph) {
@@ -311,13 +423,7 @@ int rows_levels(const Launch& L, const Grid& g, const Phys& ph) {
     if ((strips > 2 && fill < 0.71) || (L.model == 3 && (fill < 0.75 || g.nx % 64 == 0))) return 0;
     return 2;
   }
-  if (L.storage == ST_F64 && L.model == 4) return 0;  // its levels do not fit the registers
-  const int T = L.storage == ST_F64 || L.model == 4 ? 2 : 4;
-  // from 512^2 on (below, the populations sit in the L2s and the sweep is faster: 384^2 FP32
-  // 7.7 us a step against 11.6), and where the strips waste at most a quarter of their lanes
-  const int V = 64 - 2 * (T - 1), strips = (g.nx + V - 1) / V;
-  if ((long long)g.nx * g.ny * g.nz < 512 * 512 || 4LL * g.nx < 3LL * strips * V) return 0;
-  return T;
+  return by_rows(L, g) || tile_width(L, g) ? 4 : 0;
 }
 
 hipError_t launch_rows(const Launch& L, const Grid& g, void* out, const Phys& ph, int levels) {
@@ -329,13 +435,19 @@ hipError_t launch_rows(const Launch& L, const Grid& g, void* out, const Phys& ph
       default: return hipErrorInvalidValue;
     }
   }
-  const int rows = rows_for(g, levels);
-#define ROWS_CASE(S, M, T) \
-  if (L.storage == S && L.model == M && levels == T) return rows_t<S, M, T>(L, g, out, ph, rows);
-  ROWS_CASE(ST_F32, 0, 4) ROWS_CASE(ST_F32, 2, 4) ROWS_CASE(ST_F32, 3, 4)
-  ROWS_CASE(ST_F32, 0, 2) ROWS_CASE(ST_F32, 2, 2) ROWS_CASE(ST_F32, 3, 2) ROWS_CASE(ST_F32, 4, 2)
-  ROWS_CASE(ST_F64, 0, 2) ROWS_CASE(ST_F64, 2, 2) ROWS_CASE(ST_F64, 3, 2)
-#undef ROWS_CASE
+  if (by_rows(L, g) && levels == 4) {
+    switch (L.model) {
+      case 0: return rows_t<0, 4>(L, g, out, ph);
+      case 2: return rows_t<2, 4>(L, g, out, ph);
+      case 3: return rows_t<3, 4>(L, g, out, ph);
+      default: return hipErrorInvalidValue;
+    }
+  }
+#define TILES_CASE(S, M) \
+  if (L.storage == S && L.model == M) return levels == 4 ? tiles_t<S, M, 4>(L, g, out, ph) : tiles_t<S, M, 2>(L, g, out, ph);
+  TILES_CASE(ST_F32, 0) TILES_CASE(ST_F32, 2) TILES_CASE(ST_F32, 3) TILES_CASE(ST_F32, 4)
+  TILES_CASE(ST_F64, 0) TILES_CASE(ST_F64, 2) TILES_CASE(ST_F64, 3) TILES_CASE(ST_F64, 4)
+#undef TILES_CASE
   return hipErrorInvalidValue;
 }
 

@@ -119,3 +119,30 @@ def test_passes_equal_single_steps_3d(vb, model, shape, collision):  # noqa: F81
     cells = np.unique(np.concatenate([[0, shape[0] - 1, shape[0], n - 1], np.random.default_rng(1).integers(0, n, 4000)]))
     a, b = (sim.vlbm_gather_cells(cells) for sim in sims)
     assert np.abs(a - b).max() <= 1e-5 * np.abs(b).max()
+
+
+# 2D tiles: a lattice inside one tile, one cell past the 10 x 10 and 26 x 10 results, thin ones,
+# batches, one row of tiles; FP64 and 13 variables at a size of 32 x 16 tiles; large FP32 lattices
+# by rows, the last strip a quarter empty and the rows fewer than one share
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+@pytest.mark.parametrize("model,shape", [("ideal", (1, 1, 1)), ("ideal", (11, 21, 3)), ("ideal", (2, 31, 1)),
+                                         ("ideal", (131, 141, 2)), ("euler", (261, 301, 1)), ("navier_cauchy", (79, 71, 1)),
+                                         ("resistive_2d", (287, 301, 1)), ("resistive_2d", (64, 21, 1)),
+                                         ("ideal", (2670, 450, 1)), ("euler", (9000, 17, 14))])
+def test_tiles_equal_single_steps(vb, model, shape, storage):  # noqa: F811
+    """13 steps at once (a pair of 4-step passes, one of 2-step passes, one sweep) and one by
+    one: to 1e-12 (FP64), 1e-5 (FP32) of each variable's largest population, small variables a
+    tenth of the largest (a step rounds to some 1e-7 of the fluxes that enter it)."""
+    w, Q0 = _case(model, shape)
+    print("case tiles", model, shape, storage, flush=True)
+    sims = [vb.Vlbm(gpu_params(vb, w, storage)) for _ in range(2)]
+    for sim in sims:
+        sim.vlbm_init_fields(Q0)
+    sims[0].vlbm_step(13)
+    for _ in range(13):
+        sims[1].vlbm_step(1)
+    n = int(np.prod(shape))
+    cells = np.arange(n) if n < 200000 else np.unique(np.random.default_rng(1).integers(0, n, 200000))
+    a, b = (sim.vlbm_gather_cells(cells) for sim in sims)
+    scale = np.abs(b).max(axis=(0, 2), keepdims=True)
+    assert np.all(np.abs(a - b) <= (1e-12 if storage == "f64" else 1e-5) * np.maximum(scale, 0.1 * np.abs(b).max()))
