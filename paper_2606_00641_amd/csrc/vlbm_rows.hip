@@ -190,11 +190,12 @@ __global__ __launch_bounds__(TX* TY) void k_tiles(const Grid g, void* const out,
 #pragma unroll
     for (int i = 0; i < NQ; ++i) f[k][i] = get<R>(g.f, pb, k * NQ + i, o);
   const int tl = max(t - 1, 0), tr = min(t + 1, B - 1), td = max(t - TX, 0), tu = min(t + TX, B - 1);
-#pragma unroll
-  for (int lv = 0; lv < T; ++lv) {
+  // not unrolled: the collision is then compiled, and contracted, like the sweep's
+#pragma unroll 1
+  for (int lv = 0;;) {
     collide<R, 2, MODEL, COLL>(f, ph, dl);
-    if (lv == T - 1) break;
-    if (lv) __syncthreads();
+    if (++lv == T) break;
+    if (lv > 1) __syncthreads();
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
@@ -409,7 +410,8 @@ bool by_rows(const Launch& L, const Grid& g) {
 int rows_levels(const Launch& L, const Grid& g, const Phys& ph) {
   if ((L.storage != ST_F32 && L.storage != ST_F64) || ph.source != 0 || g.mask) return 0;
   if (L.dim == 3) {
-    if (L.storage != ST_F32 || L.model == 1) return 0;
+    // (the two-rate collisions of 8 and 9 variables spill: 110^3 135 us a step in place, 238 in passes)
+    if (L.storage != ST_F32 || L.model == 1 || (ph.collision && L.model != 2)) return 0;
     // From 2^18 cells on (48^3 stays in the caches: 9.4 us a step against 11.6), with planes,
     // rows and columns enough for the two planes, two of eight rows and two columns a tile
     // reads beyond its own (200^2 x 4 14.7 us against 15.9, 200 x 7 x 200 25.1 against 23.4,

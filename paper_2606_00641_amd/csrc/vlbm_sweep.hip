@@ -885,7 +885,15 @@ __global__ __launch_bounds__(256) void k_sweep2(const Grid g, const Phys ph, con
 // x row (no partial workgroup, so that every lane reaches the barriers).  It is used
 // for the 8-variable (and 5-variable) sweeps (measured on 512^3: parity 1 11-20 % faster in FP32,
 // 12 % FP16, 10 % BF16); the 26-variable sweep runs one wavefront per SIMD, where the
-// workgroup barrier leaves the CU idle, and was 16 % slower with it.
+// workgroup barrier leaves the CU idle, and was 16 % slower with it.  2D lattices in FP64
+// and FP32 do without: their single steps are no slower (8 variables FP32 64^2 4.2 -> 3.7 us,
+// 1024^2 61 -> 59, FP64 64^2 4.5 -> 3.8, 2048^2 475 and 476; 13 variables FP64 64^2 6.5 ->
+// 5.2), and are the same bits as their passes of several steps (vlbm_rows.hip), which the
+// compiler contracts like the direct form.
+template <int ST, int D, int MODEL>
+constexpr bool exchanges() {
+  return MODEL != 1 && !(D == 2 && (ST == ST_F64 || ST == ST_F32));
+}
 inline bool lane_exchange(const Grid& g, int block_x, int model) {
   return model != 1 && block_x % 64 == 0 && g.nx % block_x == 0;
 }
@@ -922,7 +930,7 @@ template <int ST, int D, int MODEL, int BODY, bool INJ>
 void launch_k(const Launch& L, dim3 grd, int parity, int coll, bool xch, bool fx, const Grid& g, const Phys& ph,
               const Codec& cd, const Body& b, const float* dq, const int* flag, const Inflow& in,
               const MomentsOut& mo = MomentsOut{}) {
-  constexpr bool kX = MODEL != 1 && (BODY == 0 || BODY == 3);  // exchange possible
+  constexpr bool kX = exchanges<ST, D, MODEL>() && (BODY == 0 || BODY == 3);  // exchange possible
   constexpr bool kF = D == 3 && MODEL == 0 && BODY != 2 && BODY != 4 && !INJ;  // x faces possible
   constexpr bool kC = !INJ;                                      // two-rate collisions possible
   auto go = [&](auto par_c, auto coll_c, auto xch_c, auto fx_c) {
@@ -932,7 +940,7 @@ void launch_k(const Launch& L, dim3 grd, int parity, int coll, bool xch, bool fx
     // the flat form differently, which moves the BF16 rounding of single populations)
     if constexpr (BODY == 0 && !FXv && !(INJ && (ST == ST_F16 || ST == ST_BF16))) {
       if (flat_rows(L, g)) {
-        hipLaunchKernelGGL((k_sweep<ST, D, MODEL, P, BODY, C, INJ, P == 1 && MODEL != 1, false, 0, true>),
+        hipLaunchKernelGGL((k_sweep<ST, D, MODEL, P, BODY, C, INJ, P == 1 && exchanges<ST, D, MODEL>(), false, 0, true>),
                            flat_grid(L, g, 1), dim3(L.block_flat), 0, L.stream, g, ph, cd, b, dq, flag, in, mo);
         return;
       }
