@@ -739,33 +739,41 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduce_grads(const float* __
   }
 }
 
-// raw moments X (FP32 channel-major [C][B][H][W]) -> standardised BF16 NHWC (C = 8)
-__global__ void k_prep(const float* __restrict__ X, int B, int C, int H, int W, const float* __restrict__ mean,
-                       const float* __restrict__ istd, bf16_t* __restrict__ out) {
-  const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;  // = b * HW + p
-  const size_t BHW = (size_t)B * H * W;
-  if (q >= BHW) return;
-  for (int c = 0; c < C; ++c) out[q * C + c] = f2bf((X[(size_t)c * BHW + q] - mean[c]) * istd[c]);
+// raw moments X (FP32 channel-major [8][positions]) -> standardised BF16, 8 channels a
+// position.  A thread takes one position and stores its channels as 16 bytes (stored one by
+// one, 384 x 192 x 192 took 199 us).
+__global__ __launch_bounds__(256) void k_prep(const float* __restrict__ X, size_t P, const float* __restrict__ mean,
+                                              const float* __restrict__ istd, bf16_t* __restrict__ out) {
+  const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= P) return;
+  float v[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) v[c] = (X[(size_t)c * P + q] - mean[c]) * istd[c];
+  *reinterpret_cast<uint4*>(out + q * 8) =
+      make_uint4(bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]), bf16_pair(v[4], v[5]), bf16_pair(v[6], v[7]));
 }
 
-// MSE on standardised outputs: y (FP32 [C][B][H][W]), target T raw -> (T - mean) * istd.
-// dZ = 2 (y - t) / n as BF16 NHWC; per-block FP64 partial sums of (y - t)^2.
-__global__ __launch_bounds__(kThreads) void k_loss(const float* __restrict__ y, const float* __restrict__ T, int B,
-                                                   int C, int H, int W, const float* __restrict__ mean,
-                                                   const float* __restrict__ istd, bf16_t* __restrict__ dz,
-                                                   double* __restrict__ partial) {
+// MSE on standardised outputs: y (FP32 [8][positions]), target T raw -> (T - mean) * istd.
+// dZ = 2 (y - t) / n as BF16, 8 channels a position, one position a thread and turn (a thread
+// per value, its dZ stored as 2 bytes of a line, took 112 us at 40 x 256^2); per-block FP64
+// partial sums of (y - t)^2.
+__global__ __launch_bounds__(kThreads) void k_loss(const float* __restrict__ y, const float* __restrict__ T, size_t P,
+                                                   const float* __restrict__ mean, const float* __restrict__ istd,
+                                                   bf16_t* __restrict__ dz, double* __restrict__ partial) {
   __shared__ double sh[kThreads / 64];
-  const size_t HW = (size_t)H * W;
-  const size_t n = (size_t)B * C * HW;
-  const double inv_n = 1.0 / (double)n;
+  const double inv_n = 1.0 / (double)(8 * P);
   double acc = 0.0;
-  for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (size_t)gridDim.x * blockDim.x) {
-    const size_t BHW = (size_t)B * HW;
-    const size_t c = q / BHW, bp = q % BHW;  // bp = b * HW + p
-    const float t = (T[q] - mean[c]) * istd[c];
-    const float d = y[q] - t;
-    acc += (double)d * (double)d;
-    dz[bp * C + c] = f2bf((float)(2.0 * inv_n) * d);
+  for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < P; q += (size_t)gridDim.x * blockDim.x) {
+    float g[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const float t = (T[(size_t)c * P + q] - mean[c]) * istd[c];
+      const float d = y[(size_t)c * P + q] - t;
+      acc += (double)d * (double)d;
+      g[c] = (float)(2.0 * inv_n) * d;
+    }
+    *reinterpret_cast<uint4*>(dz + q * 8) =
+        make_uint4(bf16_pair(g[0], g[1]), bf16_pair(g[2], g[3]), bf16_pair(g[4], g[5]), bf16_pair(g[6], g[7]));
   }
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
@@ -1281,8 +1289,7 @@ vlbm_status forward(vlbm_nn* nn, const float* X, int B, int nx, int ny, int nz, 
   if (st != VLBM_OK) return st;
   const float* norm = nn->d_norm;
   if (X) {
-    hipLaunchKernelGGL(k_prep, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, X, S, nn->cin, ny, nx,
-                       norm + 0, norm + 8, nn->d_act[0]);
+    hipLaunchKernelGGL(k_prep, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, X, P, norm + 0, norm + 8, nn->d_act[0]);
     NN_HIP(nn, hipGetLastError());
   }
   for (int l = 0; l < nn->layers; ++l) {
@@ -1528,7 +1535,7 @@ vlbm_status vlbm_nn_loss_grad(vlbm_nn* nn, const float* X, const float* T, int32
   if (st != VLBM_OK) return st;
   const int L = nn->layers;
   const int lblocks = 1024;
-  hipLaunchKernelGGL(k_loss, dim3(lblocks), dim3(kThreads), 0, nn->stream, nn->d_y, T, S, nn->cin, ny, nx,
+  hipLaunchKernelGGL(k_loss, dim3(lblocks), dim3(kThreads), 0, nn->stream, nn->d_y, T, (size_t)S * nx * ny,
                      nn->d_norm + 16, nn->d_norm + 48, nn->d_dz[0], nn->d_part_loss);
   NN_HIP(nn, hipGetLastError());
   hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(64), 0, nn->stream, nn->d_part_loss, lblocks, nn->d_loss);
