@@ -739,6 +739,129 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduce_grads(const float* __
   }
 }
 
+// ---------------------------------------------------------------------------
+// whole 3x3 network in one launch, for lattices of few tiles
+// ---------------------------------------------------------------------------
+// A workgroup computes all L layers of one 16 x 16 tile: it stages the input with the L
+// positions around it, and each layer computes one position less on every side, into LDS,
+// so that no activation passes through memory and the layers need no launches of their own.
+// Half of the wavefronts take either half of a hidden layer's 32 output channels (a
+// wavefront's weights of all layers then fit 128 registers, and four wavefronts share a
+// SIMD), each 16 consecutive positions of the layer's square at a time; the next layer's
+// weights are loaded during this one's products.  The products and the epilogue are
+// k_conv's, value for value.
+// Bound by the GELUs' vector instructions (the overlap makes 1.4 times as many) and the
+// layers' latency: 4 layers, input included, on 256^2 positions 29.3 us by layers, 26.5 with
+// 8 wavefronts that each took all 32 channels, 24.4 so; 64^2 26.2 -> 21.3, one tile 23.6 ->
+// 20.3; 3 layers 256^2 20.6 -> 16.2.
+struct NetArgs {
+  const bf16_t* w[4];
+  const float* b[4];
+  const float *oscale, *oshift;
+};
+
+constexpr int kNetThreads = 1024;
+
+// the weights and biases of a wavefront's 16 output channels, of NT such groups
+template <int CIN, int NT>
+struct NetWeights {
+  static constexpr int KS = (9 * CIN + 31) / 32;
+  bf16x8 w[KS];
+  float4 b;
+  __device__ __forceinline__ void load(const bf16_t* wpack, const float* bias, int cout) {
+    const int lane = threadIdx.x & 63, t = (threadIdx.x >> 6) % NT, co0 = 16 * t + 4 * (lane >> 4);
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      w[s] = *reinterpret_cast<const bf16x8*>(wpack + ((size_t)(s * NT + t) * 64 + lane) * 8);
+    b = co0 < cout ? *reinterpret_cast<const float4*>(bias + co0) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  }
+};
+
+// One layer from an RI x RI square of LDS; emit(co0, r, c, v) takes the lane's four output
+// channels co0.. of position (r, c) of the result's square
+template <int CIN, int NT, int RI, typename Emit>
+__device__ __forceinline__ void net_layer(const bf16_t* in, const NetWeights<CIN, NT>& q, const Emit& emit) {
+  constexpr int RO = RI - 2, KS = NetWeights<CIN, NT>::KS, NW = kNetThreads / 64;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, px = lane & 15, g = lane >> 4;
+  for (int u = wv / NT; u < (RO * RO + 15) / 16; u += NW / NT) {
+    const int p = min(16 * u + px, RO * RO - 1), r = p / RO, c = p % RO;
+    const bf16_t* base = in + (r * RI + c) * CIN;
+    f32x4 acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      bf16x8 a;
+      if constexpr (CIN == 32) {
+        a = *reinterpret_cast<const bf16x8*>(base + ((s / 3) * RI + s % 3) * CIN + 8 * g);
+      } else {  // a K step holds 4 taps, lane group g the tap 4 s + g (zero past 9)
+        const int tap = min(4 * s + g, 8);
+        a = *reinterpret_cast<const bf16x8*>(base + ((tap / 3) * RI + tap % 3) * CIN);
+        if (4 * s + 3 > 8 && 4 * s + g > 8) a = bf16x8{};
+      }
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q.w[s], a, acc, 0, 0, 0);
+    }
+    if (16 * u + px < RO * RO) emit(16 * (wv % NT) + 4 * g, r, c, acc);
+  }
+}
+
+template <int L>
+__global__ __launch_bounds__(kNetThreads, 4) void k_net(const bf16_t* __restrict__ act, const NetArgs n, int S, int H,
+                                                         int W, float* __restrict__ out) {
+  constexpr int R0 = TILE + 2 * L;
+  __shared__ __attribute__((aligned(16))) bf16_t in[R0 * R0 * 8];
+  __shared__ __attribute__((aligned(16))) bf16_t mid[2][(R0 - 2) * (R0 - 2) * 32];
+  const int g = (threadIdx.x & 63) >> 4;
+  const int tiles_x = W / TILE, ntile = tiles_x * (H / TILE);
+  const int sl = blockIdx.x / ntile, tl = blockIdx.x % ntile, ty0 = tl / tiles_x * TILE, tx0 = tl % tiles_x * TILE;
+  NetWeights<8, 2> w0;
+  NetWeights<32, 2> wh;
+  NetWeights<32, 1> wl;
+  w0.load(n.w[0], n.b[0], 32);
+  wh.load(n.w[1], n.b[1], 32);
+  const bf16_t* src = act + (size_t)sl * H * W * 8;
+  if ((int)threadIdx.x < R0 * R0) {
+    const int q = threadIdx.x, y = (ty0 - L + q / R0 + H) % H, x = (tx0 - L + q % R0 + W) % W;
+    *reinterpret_cast<uint4*>(in + q * 8) = *reinterpret_cast<const uint4*>(src + ((size_t)y * W + x) * 8);
+  }
+  static_assert(R0 * R0 <= kNetThreads, "one input position a thread");
+  auto hidden = [&](bf16_t* dst, int ro, const float4& b) {
+    return [=](int co0, int r, int c, const f32x4& v) {
+      const float4 z = make_float4(v[0] + b.x, v[1] + b.y, v[2] + b.z, v[3] + b.w);
+      *reinterpret_cast<uint2*>(dst + (r * ro + c) * 32 + co0) = gelu_bf16(z);
+    };
+  };
+  __syncthreads();
+  net_layer<8, 2, R0>(in, w0, hidden(mid[0], R0 - 2, w0.b));
+  if constexpr (L == 4) {
+    NetWeights<32, 2> w2;
+    w2.load(n.w[2], n.b[2], 32);
+    __syncthreads();
+    net_layer<32, 2, R0 - 2>(mid[0], wh, hidden(mid[1], R0 - 4, wh.b));
+    wl.load(n.w[3], n.b[3], 8);
+    __syncthreads();
+    net_layer<32, 2, R0 - 4>(mid[1], w2, hidden(mid[0], R0 - 6, w2.b));
+  } else {
+    wl.load(n.w[2], n.b[2], 8);
+    __syncthreads();
+    net_layer<32, 2, R0 - 2>(mid[0], wh, hidden(mid[1], R0 - 4, wh.b));
+  }
+  float4 sc = make_float4(0.0f, 0.0f, 0.0f, 0.0f), sh = sc;
+  if (g < 2) {
+    sc = *reinterpret_cast<const float4*>(n.oscale + 4 * g);
+    sh = *reinterpret_cast<const float4*>(n.oshift + 4 * g);
+  }
+  __syncthreads();
+  net_layer<32, 1, TILE + 2>(mid[L == 4 ? 0 : 1], wl, [&](int co0, int r, int c, const f32x4& v) {
+    if (co0 >= 8) return;
+    const size_t plane_sz = (size_t)S * H * W;
+    float* o = out + (size_t)co0 * plane_sz + ((size_t)sl * H + ty0 + r) * W + tx0 + c;
+    const float4 bs = wl.b;
+    o[0] = (v[0] + bs.x) * sc.x + sh.x;
+    o[plane_sz] = (v[1] + bs.y) * sc.y + sh.y;
+    o[2 * plane_sz] = (v[2] + bs.z) * sc.z + sh.z;
+    o[3 * plane_sz] = (v[3] + bs.w) * sc.w + sh.w;
+  });
+}
+
 // raw moments X (FP32 channel-major [8][positions]) -> standardised BF16, 8 channels a
 // position.  A thread takes one position and stores its channels as 16 bytes (stored one by
 // one, 384 x 192 x 192 took 199 us).
@@ -1278,6 +1401,11 @@ vlbm_status ensure_workspace(vlbm_nn* nn, size_t positions) {
   return VLBM_OK;
 }
 
+// 2D networks of 3 and 4 layers run in one launch (k_net) up to this many tiles, one per CU:
+// beyond, the overlap's products and GELUs cost more than the layers' launches (4 layers, input
+// included, 2 x 256^2 positions 42 us by layers and 45 in one launch, 8 x 256^2 123 and 170).
+constexpr long long kNetTiles = 256;
+
 // forward pass; mode_train keeps the pre-activations.  Writes nn->d_y (NCHW FP32),
 // scaled by oscale/oshift.
 // X == NULL: the first layer's input is already in nn->d_act[0].
@@ -1291,6 +1419,19 @@ vlbm_status forward(vlbm_nn* nn, const float* X, int B, int nx, int ny, int nz, 
   if (X) {
     hipLaunchKernelGGL(k_prep, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, s, X, P, norm + 0, norm + 8, nn->d_act[0]);
     NN_HIP(nn, hipGetLastError());
+  }
+  const long long jobs = (long long)S * (nx / TILE) * (ny / TILE);
+  if (!train && nn->nzt == 1 && (nn->layers == 3 || nn->layers == 4) && jobs <= kNetTiles) {
+    NetArgs a{};
+    for (int l = 0; l < nn->layers; ++l) a.w[l] = nn->d_wf[l], a.b[l] = nn->d_param + nn->boff[l];
+    a.oscale = oscale;
+    a.oshift = oshift;
+    if (nn->layers == 4)
+      hipLaunchKernelGGL(k_net<4>, dim3((unsigned)jobs), dim3(kNetThreads), 0, s, nn->d_act[0], a, S, ny, nx, yout);
+    else
+      hipLaunchKernelGGL(k_net<3>, dim3((unsigned)jobs), dim3(kNetThreads), 0, s, nn->d_act[0], a, S, ny, nx, yout);
+    NN_HIP(nn, hipGetLastError());
+    return VLBM_OK;
   }
   for (int l = 0; l < nn->layers; ++l) {
     const bool last = l == nn->layers - 1;

@@ -25,3 +25,24 @@ def test_forward_3d_z_shares(env, nx, ny, nz):  # noqa: F811
     net.vlbm_nn_forward(x, out)
     want = C.Net(params, layers=3, quantize=True, dim=3).forward(X)
     assert rel_l2(bm(out), want) <= 1e-2
+
+
+@pytest.mark.parametrize("layers", [3, 4])
+@pytest.mark.parametrize("B,ny,nx", [(257, 16, 16), (43, 32, 48), (2, 192, 192)])
+def test_whole_network_equals_layers(env, layers, B, ny, nx):  # noqa: F811
+    """Lattices of at most 256 tiles run the whole network in one launch, larger ones (here
+    the batch) a launch per layer: the same products in the same order, so the same bits."""
+    torch, _, nn = env
+    print("case whole network", layers, B, ny, nx, flush=True)
+    net = nn.Net(8, 32, layers, stream=torch.cuda.current_stream().cuda_stream)
+    rng = np.random.default_rng(layers)
+    net.vlbm_nn_set_weights((0.15 * rng.standard_normal(net.vlbm_nn_num_params())).astype(np.float32))
+    net.vlbm_nn_set_norm(rng.standard_normal(8), 0.5 + rng.random(8), rng.standard_normal(8), 0.5 + rng.random(8))
+    X = torch.from_numpy(rng.standard_normal((8, B, ny, nx)).astype(np.float32)).cuda()
+    whole = torch.empty_like(X)
+    net.vlbm_nn_forward(X, whole)
+    for b in range(0, B, max(1, B // 3)):
+        x = X[:, b:b + 1].contiguous()
+        y = torch.empty_like(x)
+        net.vlbm_nn_forward(x, y)
+        assert torch.equal(y, whole[:, b:b + 1]), b
