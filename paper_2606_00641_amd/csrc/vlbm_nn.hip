@@ -1111,28 +1111,37 @@ __global__ __launch_bounds__(kGateThreads) void k_gate_partials(const float* __r
 // (ncl m^2 - 2 m sum r_k)), ||divc(X + dQ)||_2 <= (1 + gb->divb_rel) ||divc(X)||_2 +
 // gb->divb_abs ||B(X)||_2 and no cell is left unphysical (partial [20]): ctl[0] = 1, else
 // ctl[0] = 0 and *fallbacks += 1.  Batch-wide
-// sums: thread t takes workgroups t, t + 256, ... in that order, wave_sum per
-// wavefront, thread 0 adds the four wavefronts in order.  (A separate launch: deciding
+// sums: wavefront w takes the sums w and w + 16, lane l the workgroups l, l + 64, ... in that
+// order, then wave_sum; a lane per channel then checks its norm (every thread adding all 21
+// sums and one thread checking the norms in turn took 6.5 us at 256^2 positions, now 4.3).  (A separate launch: deciding
 // in the last workgroup of the partials kernel needs a device-scope release fence in
 // every workgroup, which on this chip writes back L2; measured at 2D 256^2 and 3D 64^3,
 // that one kernel took longer than the two.)
-constexpr int kFinalThreads = 256;
+constexpr int kFinalThreads = 1024;
 __global__ __launch_bounds__(kFinalThreads) void k_gate_final(const double* __restrict__ partial, int nb, int gbpl,
                                                               double ncl, int project,
                                                               const GateBounds* __restrict__ gb,
                                                               int* __restrict__ ctl,
                                                               long long* __restrict__ fallbacks) {
-  constexpr int NP = kGateNP, NR = NP + 8;  // the sums, then the projection's terms
-  __shared__ double sh[kFinalThreads / 64][NR];
+  constexpr int NP = kGateNP, NW = kFinalThreads / 64;
+  __shared__ double tot[NP], proj[NW][8];  // the sums; a wavefront's part of the projection's terms
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int nblk = nb * gbpl;
-  double t[NR];
-  for (int j = 0; j < NR; ++j) t[j] = 0.0;
+  const double bound = gb->corr[lane & 7], rel = gb->divb_rel, abs_b = gb->divb_abs;
+  for (int j = wv; j < NP; j += NW) {
+    const double* q = partial + (size_t)j * nblk;
+    double s = 0.0;
 #pragma unroll 4
-  for (int w = (int)threadIdx.x; w < nblk; w += kFinalThreads)
-    for (int j = 0; j < NP; ++j) t[j] += partial[(size_t)j * nblk + w];
+    for (int w = lane; w < nblk; w += 64) s += q[w];
+    s = wave_sum(s);
+    if (lane == 0) tot[j] = s;
+  }
   // per-lattice sums of a batch (one lattice: the batch-wide sums serve, below)
-  if (project && nb > 1) {
+  const bool batch_terms = project && nb > 1;
+  if (batch_terms) {
+    double t[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) t[k] = 0.0;
     const int P = 8 * nb;
     int G = 1;
     while (G < 32 && 2 * G * P <= kFinalThreads) G *= 2;
@@ -1152,35 +1161,31 @@ __global__ __launch_bounds__(kFinalThreads) void k_gate_final(const double* __re
         const double md = m, d = ncl * md * md - 2.0 * md * s1;
 #pragma unroll
         for (int k = 0; k < 8; ++k)  // constant indices keep t in registers
-          if (k == (p & 7)) t[NP + k] += d;
+          if (k == (p & 7)) t[k] += d;
       }
     }
-  }
-  const bool batch_terms = project && nb > 1;
 #pragma unroll
-  for (int j = 0; j < NR; ++j)
-    if (j < NP || batch_terms) {
-      t[j] = wave_sum(t[j]);
-      if (lane == 0) sh[wv][j] = t[j];
-    }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-#pragma unroll
-  for (int j = 0; j < NR; ++j)
-    if (j < NP || batch_terms) {
-      t[j] = sh[0][j];
-      for (int w = 1; w < kFinalThreads / 64; ++w) t[j] += sh[w][j];
-    }
-  if (project && nb == 1)
     for (int k = 0; k < 8; ++k) {
-      const float m = (float)(t[8 + k] / ncl);
-      ctl[1 + k] = __float_as_int(m);
-      const double md = m;
-      t[NP + k] = ncl * md * md - 2.0 * md * t[8 + k];
+      t[k] = wave_sum(t[k]);
+      if (lane == 0) proj[wv][k] = t[k];
     }
-  bool ok = t[18] == 0.0 && t[20] == 0.0;
-  for (int k = 0; k < 8; ++k) ok = ok && sqrt(fmax(t[k] + t[NP + k], 0.0)) <= gb->corr[k];
-  ok = ok && sqrt(t[17]) <= (1.0 + gb->divb_rel) * sqrt(t[16]) + gb->divb_abs * sqrt(t[19]);
+  }
+  __syncthreads();
+  if (wv != 0) return;
+  const int k = lane & 7;  // lanes 8.. repeat a channel's check
+  double d = 0.0;
+  if (batch_terms) {
+    for (int w = 0; w < NW; ++w) d += proj[w][k];
+  } else if (project) {
+    const float m = (float)(tot[8 + k] / ncl);
+    if (lane < 8) ctl[1 + k] = __float_as_int(m);
+    const double md = m;
+    d = ncl * md * md - 2.0 * md * tot[8 + k];
+  }
+  const bool fine = tot[18] == 0.0 && tot[20] == 0.0 && sqrt(fmax(tot[k] + d, 0.0)) <= bound &&
+                    sqrt(tot[17]) <= (1.0 + rel) * sqrt(tot[16]) + abs_b * sqrt(tot[19]);
+  const bool ok = __all(fine);
+  if (lane != 0) return;
   ctl[0] = ok ? 1 : 0;
   if (!ok) *fallbacks += 1;
 }
