@@ -73,7 +73,7 @@ def per_parity(rows, st, d, model):
     return {p: sum(v) / len(v) for p, v in sorted(acc.items())}
 
 
-PAIR_RE = re.compile(r"k_sweep2<(\d+), (\d+), (\d+), (\d+), (\d+), (true|false), (true|false)>")
+PAIR_RE = re.compile(r"k_sweep2<(\d+), (\d+), (\d+), (\d+), (\d+), (true|false), (true|false)(?:, false)?>")
 
 
 def per_parity_pair(rows, st, d, model, body=False):
