@@ -146,3 +146,34 @@ def test_tiles_equal_single_steps(vb, model, shape, storage):  # noqa: F811
     a, b = (sim.vlbm_gather_cells(cells) for sim in sims)
     scale = np.abs(b).max(axis=(0, 2), keepdims=True)
     assert np.all(np.abs(a - b) <= (1e-12 if storage == "f64" else 1e-5) * np.maximum(scale, 0.1 * np.abs(b).max()))
+
+
+@pytest.mark.parametrize("model,shape,dim", [("ideal", (131, 47, 1), 2), ("ideal", (63, 89, 48), 3)])
+def test_passes_under_capture(vb, model, shape, dim):  # noqa: F811
+    """A captured vlbm_step(8) replayed three times, with eager work between the replays, is the
+    same 24 steps taken eagerly, bit for bit (the passes are launches and nothing else)."""
+    import torch
+    print("case capture", model, shape, flush=True)
+    if dim == 2:
+        w, Q0 = _case(model, shape)
+    else:
+        w = synth.workload_slab_3d()
+        w["shape"] = shape
+        Q0 = np.ascontiguousarray(boosted(synth.planar_discontinuity_3d(seed=5, shape=shape[::-1])[0], (0.3, -0.2, 0.25)))
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        sims = [vb.Vlbm(gpu_params(vb, w, "f32")) for _ in range(2)]
+        for sim in sims:
+            sim.vlbm_init_fields(Q0)
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            sims[0].vlbm_step(8)
+        cells = np.unique(np.random.default_rng(2).integers(0, int(np.prod(shape)), 3000))
+        for _ in range(3):
+            graph.replay()
+            torch.zeros(1000, device="cuda").add_(1.0)
+            side.synchronize()
+            sims[1].vlbm_step(8)
+            a, b = (sim.vlbm_gather_cells(cells) for sim in sims)
+            assert np.array_equal(a, b)
