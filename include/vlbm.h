@@ -210,8 +210,9 @@ vlbm_status vlbm_init_fields(vlbm_ctx* c, const void* Q, int q_on_device, int q_
  * moments, equation of state, fluxes, div B estimate, Powell source, BGK with
  * direct injection, scatter (Sec. 2.2-2.3).  Asynchronous on the context stream.  Where the
  * context has a second population buffer, groups of 8 and 4 steps from an even step on run
- * as passes of several steps each, to that buffer and back: the same arithmetic per cell,
- * rounded as the compiler contracts it there. */
+ * as passes of several steps each, to that buffer and back.  FP64 and FP32 populations of
+ * the models that have passes are the same bits however a run is split into calls, saved and
+ * restored, and whether or not there is a second buffer. */
 vlbm_status vlbm_step(vlbm_ctx* c, int32_t n);
 
 /* Moments of the current populations: Q_out SoA [K][nz][ny][nx] (FP64 or FP32,

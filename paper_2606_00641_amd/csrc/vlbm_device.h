@@ -10,6 +10,7 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
+#include "vlbm_fixed.h"
 #include "vlbm_kernels.h"
 
 namespace vlbm {

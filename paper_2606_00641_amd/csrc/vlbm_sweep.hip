@@ -357,10 +357,10 @@ __global__ __launch_bounds__(256, (MODEL == 1 && ST == ST_F32 && PAR == 0 && COL
       static_assert(D == 3 && MODEL == 0, "homogenized body: D3Q7 ideal MHD");
       R Q[K], pt;
       const bool near = HlbmTarget::near_body(bd, x, y, z);
-      collide<R, D, MODEL, COLL>(f, ph, dl, Q, pt, HlbmTarget{&bd, x, y, z, near, ph.s, ph.gm1});
+      collide_cell<ST, R, D, MODEL, COLL>(f, ph, dl, Q, pt, HlbmTarget{&bd, x, y, z, near, ph.s, ph.gm1});
     } else if constexpr (INJ && MODEL == 0) {
       R Q[K], pt;
-      collide<R, D, MODEL, COLL>(f, ph, dl, Q, pt);
+      collide_cell<ST, R, D, MODEL, COLL>(f, ph, dl, Q, pt);
       if (mo.x && own) {  // the moments the next network evaluation takes
         const size_t N = (size_t)g.nx * g.ny * g.nz;
         unsigned h[K];
@@ -381,14 +381,14 @@ __global__ __launch_bounds__(256, (MODEL == 1 && ST == ST_F32 && PAR == 0 && COL
       R sp[K], Q[K], pt;
 #pragma unroll
       for (int k = 0; k < K; ++k) sp[k] = sprev[(size_t)k * N + c];
-      collide<R, D, MODEL, COLL, NoTarget, SRC>(f, ph, dl, Q, pt, NoTarget{}, sp);
+      collide_cell<ST, R, D, MODEL, COLL, NoTarget, SRC>(f, ph, dl, Q, pt, NoTarget{}, sp);
 #pragma unroll
       for (int k = 0; k < K; ++k) sprev[(size_t)k * N + c] = sp[k];
     } else if constexpr (SRC == 1) {
       R Q[K], pt;
-      collide<R, D, MODEL, COLL, NoTarget, SRC>(f, ph, dl, Q, pt);
+      collide_cell<ST, R, D, MODEL, COLL, NoTarget, SRC>(f, ph, dl, Q, pt);
     } else {
-      collide<R, D, MODEL, COLL>(f, ph, dl);
+      collide_cell<ST, R, D, MODEL, COLL>(f, ph, dl);
     }
     if constexpr (PK) {
 #pragma unroll
@@ -486,7 +486,7 @@ __global__ __launch_bounds__(256, (MODEL == 1 && ST == ST_F32 && PAR == 0 && COL
   } else {
     static_assert(D == 3 && MODEL == 0, "body bounce-back: D3Q7 ideal MHD");
     R Q[K], pt;
-    collide<R, D, MODEL, COLL>(f, ph, dl, Q, pt);
+    collide_cell<ST, R, D, MODEL, COLL>(f, ph, dl, Q, pt);
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
       const unsigned dst = (i == 0) ? co : ((i & 1) ? np[(i - 1) >> 1] : nm[(i - 1) >> 1]);
@@ -744,7 +744,7 @@ __global__ __launch_bounds__(256) void k_sweep2(const Grid g, const Phys ph, con
       }
     }
     R dl;
-    collide<R, D, MODEL, COLL>(f, ph, dl);
+    collide_cell<ST, R, D, MODEL, COLL>(f, ph, dl);
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
@@ -888,8 +888,7 @@ __global__ __launch_bounds__(256) void k_sweep2(const Grid g, const Phys ph, con
 // workgroup barrier leaves the CU idle, and was 16 % slower with it.  2D lattices in FP64
 // and FP32 do without: their single steps are no slower (8 variables FP32 64^2 4.2 -> 3.7 us,
 // 1024^2 61 -> 59, FP64 64^2 4.5 -> 3.8, 2048^2 475 and 476; 13 variables FP64 64^2 6.5 ->
-// 5.2), and are the same bits as their passes of several steps (vlbm_rows.hip), which the
-// compiler contracts like the direct form.
+// 5.2).
 template <int ST, int D, int MODEL>
 constexpr bool exchanges() {
   return MODEL != 1 && !(D == 2 && (ST == ST_F64 || ST == ST_F32));

@@ -25,7 +25,7 @@ import os
 import re
 
 CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
-SWEEP_SOURCES = ("vlbm_device.h", "vlbm_kernels.h", "vlbm_physics.h", "vlbm_sweep.hip")
+SWEEP_SOURCES = ("vlbm_device.h", "vlbm_fixed.h", "vlbm_kernels.h", "vlbm_physics.h", "vlbm_sweep.hip")
 COPY_BYTES = 4 << 30
 
 
