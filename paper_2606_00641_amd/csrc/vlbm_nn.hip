@@ -109,7 +109,7 @@ __device__ __forceinline__ unsigned bf16_pair(float a, float b) {
 // zero): over all finite z the value here differs from erff's by less than 1.77e-7 |z|
 // (compared for every float), so where +-1.8e-7 |z| rounds to one BF16 value that is the
 // one; the rest (7 in 10^4 values of a standard normal z) take erff, one value per lane and
-// turn.
+// turn, and so do four values with an infinite one (whose |z| Phi(-|z|) here is inf x 0, NaN).
 __device__ __forceinline__ uint2 gelu_bf16(const float4 z) {
   const float zz[4] = {z.x, z.y, z.z, z.w};
   float lo[4], hi[4];
@@ -131,12 +131,14 @@ __device__ __forceinline__ uint2 gelu_bf16(const float4 z) {
   }
   uint2 v = make_uint2(bf16_pair(lo[0], lo[1]), bf16_pair(lo[2], lo[3]));
   const unsigned dx = v.x ^ bf16_pair(hi[0], hi[1]), dy = v.y ^ bf16_pair(hi[2], hi[3]);
-  if (dx | dy) {
+  const bool nan = __builtin_isunordered(lo[0], lo[1]) | __builtin_isunordered(lo[2], lo[3]);
+  if (((dx | dy) != 0) | nan) {
     unsigned left = ((dx & 0xffffu) ? 1u : 0u) | ((dx >> 16) ? 2u : 0u) | ((dy & 0xffffu) ? 4u : 0u) | ((dy >> 16) ? 8u : 0u);
+    if (nan) left = 15u;
     do {
       const int i = __ffs(left) - 1;
       const float w = i == 0 ? zz[0] : (i == 1 ? zz[1] : (i == 2 ? zz[2] : zz[3]));
-      const unsigned e = f2bf(0.5f * w * (1.0f + erff(w * 0.70710678118654752f)));
+      const unsigned e = bf16_pair(0.5f * w * (1.0f + erff(w * 0.70710678118654752f)), 0.0f);
       if (i == 0) v.x = (v.x & 0xffff0000u) | e;
       if (i == 1) v.x = (v.x & 0xffffu) | (e << 16);
       if (i == 2) v.y = (v.y & 0xffff0000u) | e;
