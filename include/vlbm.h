@@ -193,11 +193,14 @@ vlbm_status vlbm_params_default(vlbm_params* p);
 /* Bytes of the population buffer for these parameters (K*Q padded planes). */
 vlbm_status vlbm_population_bytes(const vlbm_params* p, size_t* bytes);
 
+/* Bytes of the second population buffer that vlbm_step takes for passes of several steps
+ * (vlbm_set_passes) on this lattice: 0 where it takes none, else vlbm_population_bytes().
+ * Most 2D lattices in FP64/FP32 storage, and periodic 3D lattices in FP32 storage of up to
+ * 9 variables from 2^18 cells on, have such passes, up to 4.5 GiB. */
+vlbm_status vlbm_pass_bytes(const vlbm_params* p, size_t* bytes);
+
 /* Create a context: validate p, allocate (or adopt) the population buffer and the
- * small FP64 reduction buffers.  Most 2D lattices in FP64/FP32 storage, and periodic 3D
- * lattices in FP32 storage of up to 9 variables from 2^18 cells on, also take a second
- * population buffer (up to 4.5 GiB; without it, or if it cannot be had, every step
- * sweeps in place).  No kernel runs.  *out is NULL on error. */
+ * small FP64 reduction buffers.  No kernel runs.  *out is NULL on error. */
 vlbm_status vlbm_create(const vlbm_params* p, vlbm_ctx** out);
 
 /* f := f^eq(Q) in every cell (natural layout), step counter := 0.  Q is SoA
@@ -209,11 +212,20 @@ vlbm_status vlbm_init_fields(vlbm_ctx* c, const void* Q, int q_on_device, int q_
 /* Advance n >= 0 steps: per cell, gather the populations (in-place AA pattern),
  * moments, equation of state, fluxes, div B estimate, Powell source, BGK with
  * direct injection, scatter (Sec. 2.2-2.3).  Asynchronous on the context stream.  Where the
- * context has a second population buffer, groups of 8 and 4 steps from an even step on run
- * as passes of several steps each, to that buffer and back.  FP64 and FP32 populations of
+ * lattice has passes of several steps (vlbm_pass_bytes) and they are on (vlbm_set_passes),
+ * groups of 8 and 4 steps from an even step on run as such passes, to a second population
+ * buffer and back; the first of them allocates the buffer, and if it cannot be had every
+ * step sweeps in place.  FP64 and FP32 populations of
  * the models that have passes are the same bits however a run is split into calls, saved and
  * restored, and whether or not there is a second buffer. */
 vlbm_status vlbm_step(vlbm_ctx* c, int32_t n);
+
+/* Whether vlbm_step may take a second population buffer and run passes of several steps:
+ * 1, the default of a context that allocates its population buffer, or 0, the default of
+ * one that adopts it.  0 frees a second buffer that has been taken (after the stream's
+ * work; a captured graph of passes must not be replayed any more), 1 also asks again for
+ * one that could not be had. */
+vlbm_status vlbm_set_passes(vlbm_ctx* c, int32_t on);
 
 /* Moments of the current populations: Q_out SoA [K][nz][ny][nx] (FP64 or FP32,
  * host or device; may be NULL) and totals (host, may be NULL, K + 5 doubles):

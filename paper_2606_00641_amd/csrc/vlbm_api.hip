@@ -69,9 +69,55 @@ long long plane_stride(long long N, int esize) {
   return bytes / esize;
 }
 
+size_t population_bytes(const vlbm_params* p) {
+  const int es = esize_of(p->storage);
+  return (size_t)nvars_of(p->model) * (2 * dim_of(p->lattice) + 1) *
+         plane_stride((long long)p->nx * p->ny * p->nz, es) * es;
+}
+
 // The multi-step passes need a second population buffer; it is taken up to
 // this size (1.6 % of the card; 4096^2 cells of 13 variables in FP32).
 constexpr size_t kRowsBytes = (size_t)9 << 29;
+
+// Steps per multi-step pass on the lattice of valid parameters (0: every step sweeps).
+int pass_levels(const vlbm_params* p) {
+  if (population_bytes(p) > kRowsBytes || p->body) return 0;
+  for (int f = 0; f < 6; ++f)
+    if (p->bc[f] != VLBM_BC_PERIODIC) return 0;
+  Launch L{};
+  L.storage = p->storage;
+  L.dim = dim_of(p->lattice);
+  L.model = p->model;
+  Grid g{};
+  g.nx = p->nx;
+  g.ny = p->ny;
+  g.nz = p->nz;
+  Phys ph{};
+  ph.collision = p->collision;
+  ph.source = p->source;
+  return rows_levels(L, g, ph);
+}
+
+// Whether a pass can run now: the second buffer is taken on the context's device when the
+// first pass asks for it, and kept for the later ones.  The step may be captured, on this
+// stream or another; an allocation is no part of the graph, and the relaxed mode lets it
+// through.
+bool pass_ready(vlbm_ctx* c) {
+  if (!c->passes || c->d_alt) return c->passes;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  int dev = c->device;
+  (void)hipGetDevice(&dev);
+  if (dev != c->device) (void)hipSetDevice(c->device);
+  c->passes = hipMalloc(&c->d_alt, c->pop_bytes) == hipSuccess;
+  if (dev != c->device) (void)hipSetDevice(dev);
+  if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (!c->passes) {
+    (void)hipGetLastError();
+    c->d_alt = nullptr;
+  }
+  return c->passes;
+}
 
 vlbm_status validate(const vlbm_params* p) {
   if (!p) return fail(nullptr, VLBM_ERR_ARG, "params is NULL");
@@ -339,9 +385,15 @@ vlbm_status vlbm_population_bytes(const vlbm_params* p, size_t* bytes) {
   vlbm_status s = validate(p);
   if (s != VLBM_OK) return s;
   if (!bytes) return VLBM_ERR_ARG;
-  const int D = dim_of(p->lattice), K = nvars_of(p->model), es = esize_of(p->storage);
-  const long long N = (long long)p->nx * p->ny * p->nz;
-  *bytes = (size_t)K * (2 * D + 1) * plane_stride(N, es) * es;
+  *bytes = population_bytes(p);
+  return VLBM_OK;
+}
+
+vlbm_status vlbm_pass_bytes(const vlbm_params* p, size_t* bytes) {
+  vlbm_status s = validate(p);
+  if (s != VLBM_OK) return s;
+  if (!bytes) return VLBM_ERR_ARG;
+  *bytes = pass_levels(p) ? population_bytes(p) : 0;
   return VLBM_OK;
 }
 
@@ -360,7 +412,7 @@ vlbm_status vlbm_create(const vlbm_params* p, vlbm_ctx** out) {
   c->esize = esize_of(p->storage);
   c->N = (long long)p->nx * p->ny * p->nz;
   c->stride = plane_stride(c->N, c->esize);
-  c->pop_bytes = (size_t)c->K * c->NQ * c->stride * c->esize;
+  c->pop_bytes = population_bytes(p);
   c->stream = static_cast<hipStream_t>(p->stream);
   static std::atomic<long long> next_uid{1};
   c->uid = next_uid++;
@@ -502,14 +554,8 @@ vlbm_status vlbm_create(const vlbm_params* p, vlbm_ctx** out) {
   c->L.block_x = p->block_x ? p->block_x : (p->nx >= 256 ? 256 : (p->nx >= 128 ? 128 : 64));
   c->L.block_flat = p->block_x ? p->block_x : (c->N < 256 * 256 ? 64 : 256);
   c->L.stream = c->stream;
-  // the multi-step passes' second buffer, on lattices they gain on; without it every step
-  // sweeps in place
-  if (c->pop_bytes <= kRowsBytes && !c->has_faces && !p->body) c->levels = rows_levels(c->L, c->g, c->ph);
-  if (c->levels && hipMalloc(&c->d_alt, c->pop_bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    c->d_alt = nullptr;
-    c->levels = 0;
-  }
+  c->levels = pass_levels(p);
+  c->passes = c->owned;  // a caller who brings the buffer says where memory goes
   *out = c;
   return VLBM_OK;
 }
@@ -591,7 +637,7 @@ vlbm_status vlbm_step(vlbm_ctx* c, int32_t n) {
     // two passes of t steps each, to the second buffer and back, from an even step on
     int t = c->step & 1 ? 0 : c->levels;
     if (t > 2 && left < 2 * t) t = 2;
-    if (t && left >= 2 * t) {
+    if (t && left >= 2 * t && pass_ready(c)) {
       Grid there = c->g;
       there.f = c->d_alt;
       hipError_t e = launch_rows(c->L, c->g, c->d_alt, c->ph, t);
@@ -604,6 +650,18 @@ vlbm_status vlbm_step(vlbm_ctx* c, int32_t n) {
     const vlbm_status s = vlbm_step_one(c);
     if (s != VLBM_OK) return s;
     --left;
+  }
+  return VLBM_OK;
+}
+
+vlbm_status vlbm_set_passes(vlbm_ctx* c, int32_t on) {
+  if (!c) return VLBM_ERR_ARG;
+  if (on != 0 && on != 1) return fail(c, VLBM_ERR_ARG, "on = %d must be 0 or 1", on);
+  c->passes = on == 1;
+  if (!c->passes && c->d_alt) {
+    VLBM_HIP(c, hipStreamSynchronize(c->stream));  // passes in flight
+    VLBM_HIP(c, hipFree(c->d_alt));
+    c->d_alt = nullptr;
   }
   return VLBM_OK;
 }

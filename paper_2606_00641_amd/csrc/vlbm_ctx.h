@@ -31,8 +31,9 @@ struct vlbm_ctx {
   double* d_totals = nullptr;    // [K+5] totals, then 3 x KMAX codec scratch
   double* d_Q = nullptr;         // [q_planes][N] moments scratch (lazy, grown)
   size_t q_planes = 0;
-  void* d_alt = nullptr;          // second population buffer of the multi-step passes (may be NULL)
-  int levels = 0;                 // steps per multi-step pass (0: none)
+  void* d_alt = nullptr;          // second population buffer of the multi-step passes (lazy)
+  int levels = 0;                 // steps per multi-step pass on this lattice (0: none)
+  bool passes = false;            // they may run: asked for, and their buffer not refused
   bool has_faces = false;         // some face is not periodic
   vlbm::Inflow inflow{};
   vlbm::Body body{};              // geometry; t and box set per launch

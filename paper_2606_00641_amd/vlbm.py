@@ -97,6 +97,8 @@ def load_library(path: str = LIB_PATH):
     sigs = {
         "vlbm_params_default": [P],
         "vlbm_population_bytes": [P, ctypes.POINTER(ctypes.c_size_t)],
+        "vlbm_pass_bytes": [P, ctypes.POINTER(ctypes.c_size_t)],
+        "vlbm_set_passes": [vp, ctypes.c_int32],
         "vlbm_create": [P, ctypes.POINTER(vp)],
         "vlbm_init_fields": [vp, vp, ctypes.c_int, ctypes.c_int],
         "vlbm_step": [vp, ctypes.c_int32],
@@ -241,6 +243,16 @@ class Vlbm:
 
     def vlbm_step(self, n):
         _check(_lib.vlbm_step(self.ctx, int(n)), self.ctx)
+
+    def vlbm_set_passes(self, on):
+        """Whether vlbm_step may take a second population buffer for passes of several steps."""
+        _check(_lib.vlbm_set_passes(self.ctx, 1 if on else 0), self.ctx)
+
+    def pass_bytes(self):
+        """Bytes of that second buffer on this lattice (0: it has no such passes)."""
+        n = ctypes.c_size_t()
+        _check(_lib.vlbm_pass_bytes(ctypes.byref(self.params), ctypes.byref(n)))
+        return n.value
 
     def vlbm_moments(self, out=None, f32=False, with_field=True, raise_nonfinite=True):
         """Returns (Q [K, N] numpy FP64/FP32 or the given torch tensor, totals [K+5])."""
