@@ -372,6 +372,10 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_cols(const Grid g, void* 
   }
 }
 
+// Models whose two-rate collisions k_cols takes (those of 8 and 9 variables spill: 110^3 135 us
+// a step in place, 238 in passes).
+constexpr bool cols_two_rate(int model) { return model == 2; }
+
 template <int MODEL>
 hipError_t cols_t(const Launch& L, const Grid& g, void* out, const Phys& ph) {
   const int strips = (g.nx + kColV - 1) / kColV, V = std::min(kColV, ((g.nx + strips - 1) / strips + 7) / 8 * 8);
@@ -386,10 +390,14 @@ hipError_t cols_t(const Launch& L, const Grid& g, void* out, const Phys& ph) {
     if (best < 0 || cost < best) best = cost, planes = p;
   }
   const dim3 grd((unsigned)(cols * ((g.nz + planes - 1) / planes))), blk(64 * kColWaves);
-  if (ph.collision)
-    hipLaunchKernelGGL((k_cols<MODEL, 1>), grd, blk, 0, L.stream, g, out, ph, V, planes);
-  else
-    hipLaunchKernelGGL((k_cols<MODEL, 0>), grd, blk, 0, L.stream, g, out, ph, V, planes);
+  if (ph.collision) {
+    if constexpr (cols_two_rate(MODEL)) {
+      hipLaunchKernelGGL((k_cols<MODEL, 1>), grd, blk, 0, L.stream, g, out, ph, V, planes);
+      return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
+  }
+  hipLaunchKernelGGL((k_cols<MODEL, 0>), grd, blk, 0, L.stream, g, out, ph, V, planes);
   return hipGetLastError();
 }
 
@@ -410,8 +418,7 @@ bool by_rows(const Launch& L, const Grid& g) {
 int rows_levels(const Launch& L, const Grid& g, const Phys& ph) {
   if ((L.storage != ST_F32 && L.storage != ST_F64) || ph.source != 0 || g.mask) return 0;
   if (L.dim == 3) {
-    // (the two-rate collisions of 8 and 9 variables spill: 110^3 135 us a step in place, 238 in passes)
-    if (L.storage != ST_F32 || L.model == 1 || (ph.collision && L.model != 2)) return 0;
+    if (L.storage != ST_F32 || L.model == 1 || (ph.collision && !cols_two_rate(L.model))) return 0;
     // From 2^18 cells on (48^3 stays in the caches: 9.4 us a step against 11.6), with planes,
     // rows and columns enough for the two planes, two of eight rows and two columns a tile
     // reads beyond its own (200^2 x 4 14.7 us against 15.9, 200 x 7 x 200 25.1 against 23.4,
