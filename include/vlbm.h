@@ -47,7 +47,7 @@ typedef struct vlbm_ctx vlbm_ctx;
 typedef enum {
   VLBM_OK = 0,
   VLBM_ERR_ARG = -1,       /* invalid argument or parameter */
-  VLBM_ERR_OOM = -2,       /* device allocation failed */
+  VLBM_ERR_OOM = -2,       /* an allocation failed, on the device or the host */
   VLBM_ERR_HIP = -3,       /* a HIP runtime call failed */
   VLBM_ERR_STATE = -4,     /* call out of order (e.g. step before init) */
   VLBM_ERR_NONFINITE = -5  /* moments found rho <= 0, p < 0 or a non-finite value */

@@ -8,10 +8,10 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
-#include <vector>
 
 #include "vlbm.h"
 #include "vlbm_ctx.h"
@@ -670,6 +670,11 @@ vlbm_status vlbm_moments(vlbm_ctx* c, void* Q_out, int out_on_device, int out_is
   if (!c) return VLBM_ERR_ARG;
   if (!c->initialized) return fail(c, VLBM_ERR_STATE, "vlbm_moments before vlbm_init_fields");
   const size_t nq = (size_t)c->K * c->N;
+  std::unique_ptr<double[]> h;  // FP64 moments on their way to an FP32 host array
+  if (Q_out && !out_on_device && out_is_f32) {
+    h.reset(new (std::nothrow) double[nq]);
+    if (!h) return fail(c, VLBM_ERR_OOM, "host allocation of %zu moments failed", nq);
+  }
   const bool has_B = c->p.model == VLBM_IDEAL || c->p.model == VLBM_RESISTIVE || c->p.model == VLBM_RESISTIVE_2D;
   const int bx = c->p.model == VLBM_RESISTIVE_2D ? 4 : 5;
   // the whole FP64 field only where it is the result or goes to the host
@@ -696,19 +701,13 @@ vlbm_status vlbm_moments(vlbm_ctx* c, void* Q_out, int out_on_device, int out_is
   if (has_B) VLBM_HIP(c, launch_divc(c->L, c->g, B, c->d_partial2, c->nblk));
   VLBM_HIP(c, reduce_totals(c, NT, has_B, c->d_partial, c->d_partial2, c->d_totals));
   double tot[KMAX + 5];
-  VLBM_HIP(c, hipMemcpyAsync(tot, c->d_totals, sizeof(double) * NT, hipMemcpyDeviceToHost, c->stream));
-  std::vector<double> h;
-  if (field && !out_on_device) {
-    void* dst = Q_out;
-    if (out_is_f32) {
-      h.resize(nq);
-      dst = h.data();
-    }
-    VLBM_HIP(c, hipMemcpyAsync(dst, out.q64, sizeof(double) * nq, hipMemcpyDeviceToHost, c->stream));
-  }
-  VLBM_HIP(c, hipStreamSynchronize(c->stream));
+  hipError_t e = hipMemcpyAsync(tot, c->d_totals, sizeof(double) * NT, hipMemcpyDeviceToHost, c->stream);
+  if (e == hipSuccess && field && !out_on_device)
+    e = hipMemcpyAsync(h ? h.get() : Q_out, out.q64, sizeof(double) * nq, hipMemcpyDeviceToHost, c->stream);
+  const hipError_t se = hipStreamSynchronize(c->stream);  // also on an error: tot and h must outlive the copies
+  if (e != hipSuccess || se != hipSuccess) return hip_fail(c, e != hipSuccess ? e : se, "copy of the moments");
   if (!has_B) tot[c->K + 3] = 0.0;  // no field, no divergence
-  if (!h.empty()) {
+  if (h) {
     float* o = static_cast<float*>(Q_out);
     for (size_t j = 0; j < nq; ++j) o[j] = (float)h[j];
   }
