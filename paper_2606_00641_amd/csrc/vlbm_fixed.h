@@ -46,11 +46,10 @@ __device__ __forceinline__ void flux(const R* Q, const R* Jb, const Phys& ph, R 
       for (int b = 0; b < 3; ++b)
 #pragma unroll
         for (int c = b; c < 3; ++c) {
-          const R shear = (a == b ? v[c] : R(0)) + (a == c ? v[b] : R(0));
           if (b == c)
-            P[sigma_index(b, c)][a] = -(lam * v[a] + mu * shear);
+            P[sigma_index(b, c)][a] = a == b ? -(lam * v[a] + mu * (v[a] + v[a])) : -(lam * v[a] + R(0));
           else
-            P[sigma_index(b, c)][a] = -(R(0) + mu * shear);
+            P[sigma_index(b, c)][a] = a == b ? -(R(0) + mu * v[c]) : (a == c ? -(R(0) + mu * v[b]) : -R(0));
         }
     }
   } else if constexpr (MODEL == 2) {
@@ -215,11 +214,17 @@ __device__ __forceinline__ void collide(R (*f)[2 * D + 1], const Phys& ph, R& dl
       const R swi = wi * S[k];
       const R d0 = w0 * Qt[k] - f[k][0];
       f[k][0] += linear ? w0 * S[k] + om * d0 : om * d0 + sw0;
+      // one operation of all directions after the other, not one direction after the other: in
+      // that order neighbouring instructions do not wait for each other
+      R r[2 * D];
 #pragma unroll
-      for (int a = 0; a < D; ++a) {
-        f[k][2 * a + 1] += om * (wi * (Qt[k] + P[k][a] * c) - f[k][2 * a + 1]) + swi;
-        f[k][2 * a + 2] += om * (wi * (Qt[k] - P[k][a] * c) - f[k][2 * a + 2]) + swi;
-      }
+      for (int i = 0; i < 2 * D; ++i) r[i] = i & 1 ? Qt[k] - P[k][i / 2] * c : Qt[k] + P[k][i / 2] * c;
+#pragma unroll
+      for (int i = 0; i < 2 * D; ++i) r[i] = wi * r[i] - f[k][i + 1];
+#pragma unroll
+      for (int i = 0; i < 2 * D; ++i) r[i] = om * r[i] + swi;
+#pragma unroll
+      for (int i = 0; i < 2 * D; ++i) f[k][i + 1] += r[i];
     } else {
       const R oa = R(ph.omega[k]), os = R(ph.omega_s[k]), od = R(ph.omega_d[k]);
       const R d0 = w0 * Qt[k] - f[k][0];

@@ -165,8 +165,11 @@ hipError_t rows_t(const Launch& L, const Grid& g, void* out, const Phys& ph) {
 // variables FP64 64^2 4.6 -> 2.3 us, 256^2 8.0 -> 5.0, 1024^2 124 -> 70 (k_rows 86); FP32
 // 64^2 4.3 -> 1.8, 512^2 18 -> 7.1 (k_rows 12.3); 13 variables FP64 64^2 6.6 -> 3.5, 2000^2
 // 838 -> 649, FP32 256^2 9.0 -> 4.7, 2000^2 405 -> 267 (k_rows, 2 levels, 294).
+// 5 variables in FP64 are held to 128 VGPRs, four wavefronts per SIMD, for which their LDS leaves
+// room (at 130: 2000^2 114 -> 147 us a step).
 template <int ST, int MODEL, int T, int TX, int TY, int COLL>
-__global__ __launch_bounds__(TX* TY) void k_tiles(const Grid g, void* const out, const Phys ph) {
+__global__ __launch_bounds__(TX* TY, ST == ST_F64 && MODEL == 2 ? 4 : 1) void k_tiles(const Grid g, void* const out,
+                                                                                      const Phys ph) {
   using R = typename Store<ST>::R;
   constexpr int NQ = 5, K = kNVars<MODEL>, B = TX * TY, H = T - 1, IX = TX - 2 * H, IY = TY - 2 * H;
   constexpr unsigned ES = sizeof(R);
