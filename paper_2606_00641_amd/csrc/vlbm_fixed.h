@@ -1,6 +1,6 @@
-// The cell's collision with its rounding stated, for FP64 and FP32 populations of the ideal,
-// Euler, Navier-Cauchy and 13-component models (vlbm_physics.h defines the method and serves
-// the rest).
+// The cell's collision with its rounding stated, for the ideal, Euler, Navier-Cauchy and
+// 13-component models in the kernels that have to agree with one another, below
+// (vlbm_physics.h defines the method and serves the rest).
 //
 // The populations of these models advance in kernels of several forms: in place, with and
 // without the exchange between lanes, by rows and flat, injecting, and several steps in a
@@ -17,10 +17,15 @@
 
 namespace vlbm {
 
-// The 26-component model and the Guo and Chai sources have kernels of one form, and 16-bit
-// storage has no passes.
-template <int ST, int MODEL, int SRC>
-inline constexpr bool kFixedRounding = (ST == 0 || ST == 1) && MODEL != 1 && SRC == 0;
+// The 26-component model and the Guo and Chai sources have kernels of one form.  3D lattices
+// in FP64 have no passes, and of these models only the ideal one has an injecting sweep.
+// 16-bit storage has no passes either, and where the workgroups tile the x rows it keeps the rounding its kernels have
+// always had; on other lattices its flat sweeps (FLAT) give the bits of the injecting sweep,
+// which takes them by rows, so that a corrected run that corrects nothing is the plain run
+// there too.
+template <int ST, int D, int MODEL, int SRC, bool FLAT>
+inline constexpr bool kFixedRounding =
+    MODEL != 1 && SRC == 0 && (ST == 1 || (ST == 0 ? D == 2 || MODEL == 0 : FLAT));
 
 namespace fixed {
 
@@ -253,19 +258,19 @@ __device__ __forceinline__ void collide(R (*f)[2 * D + 1], const Phys& ph, R& dl
 }  // namespace fixed
 
 // One collision of a cell of storage form ST.
-template <int ST, typename R, int D, int MODEL, int COLL = 0, typename Tgt = NoTarget, int SRC = 0>
+template <int ST, typename R, int D, int MODEL, int COLL = 0, typename Tgt = NoTarget, int SRC = 0, bool FLAT = false>
 __device__ __forceinline__ void collide_cell(R (*f)[2 * D + 1], const Phys& ph, R& dlat, R (&Q)[kNVars<MODEL>], R& pt,
                                              const Tgt& tgt = Tgt{}, R* sp = nullptr) {
-  if constexpr (kFixedRounding<ST, MODEL, SRC>)
+  if constexpr (kFixedRounding<ST, D, MODEL, SRC, FLAT>)
     fixed::collide<R, D, MODEL, COLL>(f, ph, dlat, Q, pt, tgt);
   else
     collide<R, D, MODEL, COLL, Tgt, SRC>(f, ph, dlat, Q, pt, tgt, sp);
 }
-template <int ST, typename R, int D, int MODEL, int COLL = 0>
+template <int ST, typename R, int D, int MODEL, int COLL = 0, bool FLAT = false>
 __device__ __forceinline__ void collide_cell(R (*f)[2 * D + 1], const Phys& ph, R& dlat) {
   R Q[kNVars<MODEL>];
   R pt;
-  collide_cell<ST, R, D, MODEL, COLL>(f, ph, dlat, Q, pt);
+  collide_cell<ST, R, D, MODEL, COLL, NoTarget, 0, FLAT>(f, ph, dlat, Q, pt);
 }
 
 }  // namespace vlbm

@@ -388,7 +388,7 @@ __global__ __launch_bounds__(256, (MODEL == 1 && ST == ST_F32 && PAR == 0 && COL
       R Q[K], pt;
       collide_cell<ST, R, D, MODEL, COLL, NoTarget, SRC>(f, ph, dl, Q, pt);
     } else {
-      collide_cell<ST, R, D, MODEL, COLL>(f, ph, dl);
+      collide_cell<ST, R, D, MODEL, COLL, FLAT>(f, ph, dl);
     }
     if constexpr (PK) {
 #pragma unroll
@@ -744,7 +744,7 @@ __global__ __launch_bounds__(256) void k_sweep2(const Grid g, const Phys ph, con
       }
     }
     R dl;
-    collide_cell<ST, R, D, MODEL, COLL>(f, ph, dl);
+    collide_cell<ST, R, D, MODEL, COLL, FLAT>(f, ph, dl);
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
@@ -912,8 +912,8 @@ inline bool flat_rows(const Launch& L, const Grid& g) {
 }
 // Two cells per lane from this many cells on (256 workgroups of 512 cells, one per CU):
 // on a 76 x 78 lattice, 12 workgroups, they took 16.6 us a step against 14.4 us.  D3Q7 only:
-// on D2Q5 the compiler contracts the pair form's arithmetic differently from the one-cell
-// sweep these lattices took before, which moves the 16-bit rounding of single populations.
+// the D2Q5 form was left out while the compiler chose the rounding of each form, and has not
+// been measured since.
 constexpr long long kFlatPairCells = 256 * 512;
 inline dim3 flat_grid(const Launch& L, const Grid& g, int cells_per_lane) {
   const long long per = (long long)L.block_flat * cells_per_lane, n = (long long)g.nx * g.ny * g.nz;
@@ -935,8 +935,8 @@ void launch_k(const Launch& L, dim3 grd, int parity, int coll, bool xch, bool fx
   auto go = [&](auto par_c, auto coll_c, auto xch_c, auto fx_c) {
     constexpr int P = decltype(par_c)::value, C = decltype(coll_c)::value;
     constexpr bool X = decltype(xch_c)::value, FXv = decltype(fx_c)::value;
-    // (the injecting sweep in 16-bit storage keeps its row workgroups: the compiler contracts
-    // the flat form differently, which moves the BF16 rounding of single populations)
+    // (the injecting sweep in 16-bit storage keeps its row workgroups: its flat form was left out
+    // while the compiler chose the rounding of each, and has not been measured since)
     if constexpr (BODY == 0 && !FXv && !(INJ && (ST == ST_F16 || ST == ST_BF16))) {
       if (flat_rows(L, g)) {
         hipLaunchKernelGGL((k_sweep<ST, D, MODEL, P, BODY, C, INJ, P == 1 && exchanges<ST, D, MODEL>(), false, 0, true>),

@@ -87,3 +87,22 @@ def test_zero_network_on_lattices_of_passes(vb, shape, dim):  # noqa: F811
     want = plain.vlbm_get_populations()[0]
     assert np.array_equal(zero.vlbm_get_populations()[0], want)
     assert np.array_equal(held.vlbm_get_populations()[0], want)
+
+
+@pytest.mark.parametrize("storage", ["f16", "bf16"])
+@pytest.mark.parametrize("shape,dim", [((48, 32, 16), 3), ((80, 64, 32), 3), ((208, 32, 48), 3), ((80, 48, 1), 2),
+                                       ((144, 96, 3), 2)])
+def test_zero_network_on_flat_rows_16_bit(vb, shape, dim, storage):  # noqa: F811
+    """The same in FP16 and BF16 storage on rows the workgroups do not tile: the plain sweep takes
+    them flat, one and (the two large 3D lattices) two cells a lane, the injecting sweep by rows."""
+    import torch
+    from paper_2606_00641_amd import nn
+    w, Q0 = _state("ideal", shape, dim)
+    print("case zero network 16 bit", shape, storage, flush=True)
+    plain, zero = (vb.Vlbm(gpu_params(vb, w, storage)) for _ in range(2))
+    for sim in (plain, zero):
+        sim.vlbm_init_fields(Q0)
+    net = nn.Net(8, 32, 3, stream=torch.cuda.current_stream().cuda_stream, dim=dim)
+    assert nn.vlbm_step_corrected(zero, net, 40, np.full(8, 1e30), 0.1) == 0
+    plain.vlbm_step(40)
+    assert np.array_equal(zero.vlbm_get_populations()[0], plain.vlbm_get_populations()[0])
