@@ -17,12 +17,13 @@
 
 namespace vlbm {
 
-// The 26-component model and the Guo and Chai sources have kernels of one form.  3D lattices
-// in FP64 have no passes, and of these models only the ideal one has an injecting sweep.
-// 16-bit storage has no passes either, and where the workgroups tile the x rows it keeps the rounding its kernels have
-// always had; on other lattices its flat sweeps (FLAT) give the bits of the injecting sweep,
-// which takes them by rows, so that a corrected run that corrects nothing is the plain run
-// there too.
+// Where the rounding has to be stated: periodic lattices without a body (the others have one
+// step of one form) of the models above (the 26-component model and the Guo and Chai sources
+// have kernels of one form), in FP32; in FP64 where there are passes (2D) or an injecting
+// sweep (the ideal model); and in the flat 16-bit sweeps (FLAT), which then give the bits of
+// the injecting sweep that takes the same lattices by rows, so that a corrected run that
+// corrects nothing is the plain run.  On rows that the workgroups tile, 16-bit storage keeps
+// the rounding its kernels have always had.
 template <int ST, int D, int MODEL, int SRC, bool FLAT>
 inline constexpr bool kFixedRounding =
     MODEL != 1 && SRC == 0 && (ST == 1 || (ST == 0 ? D == 2 || MODEL == 0 : FLAT));
@@ -257,20 +258,20 @@ __device__ __forceinline__ void collide(R (*f)[2 * D + 1], const Phys& ph, R& dl
 
 }  // namespace fixed
 
-// One collision of a cell of storage form ST.
-template <int ST, typename R, int D, int MODEL, int COLL = 0, typename Tgt = NoTarget, int SRC = 0, bool FLAT = false>
+// One collision of a cell, its rounding stated (FIXED) or the compiler's.
+template <bool FIXED, typename R, int D, int MODEL, int COLL = 0, typename Tgt = NoTarget, int SRC = 0>
 __device__ __forceinline__ void collide_cell(R (*f)[2 * D + 1], const Phys& ph, R& dlat, R (&Q)[kNVars<MODEL>], R& pt,
                                              const Tgt& tgt = Tgt{}, R* sp = nullptr) {
-  if constexpr (kFixedRounding<ST, D, MODEL, SRC, FLAT>)
+  if constexpr (FIXED)
     fixed::collide<R, D, MODEL, COLL>(f, ph, dlat, Q, pt, tgt);
   else
     collide<R, D, MODEL, COLL, Tgt, SRC>(f, ph, dlat, Q, pt, tgt, sp);
 }
-template <int ST, typename R, int D, int MODEL, int COLL = 0, bool FLAT = false>
+template <bool FIXED, typename R, int D, int MODEL, int COLL = 0>
 __device__ __forceinline__ void collide_cell(R (*f)[2 * D + 1], const Phys& ph, R& dlat) {
   R Q[kNVars<MODEL>];
   R pt;
-  collide_cell<ST, R, D, MODEL, COLL, NoTarget, 0, FLAT>(f, ph, dlat, Q, pt);
+  collide_cell<FIXED, R, D, MODEL, COLL>(f, ph, dlat, Q, pt);
 }
 
 }  // namespace vlbm

@@ -88,7 +88,7 @@ __global__ __launch_bounds__(256) void k_rows(const Grid g, void* const out, con
     yr = yr + 1 == ny ? 0 : yr + 1;
     if (j + 1 < nj) load(nf, yr);
     R dl;
-    collide_cell<ST_F32, R, 2, MODEL, COLL>(f, ph, dl);
+    collide_cell<true, R, 2, MODEL, COLL>(f, ph, dl);
 #pragma unroll
     for (int t = 0; t < T - 1; ++t) {
       R h[K][NQ];
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(256) void k_rows(const Grid g, void* const out, con
         C[t][k][4] = f[k][3];
       }
       // level t + 2 begins with the row whose neighbours have both passed level t + 1
-      if (j >= 2 * (t + 1)) collide_cell<ST_F32, R, 2, MODEL, COLL>(h, ph, dl);
+      if (j >= 2 * (t + 1)) collide_cell<true, R, 2, MODEL, COLL>(h, ph, dl);
 #pragma unroll
       for (int k = 0; k < K; ++k)
 #pragma unroll
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(TX* TY, ST == ST_F64 && MODEL == 2 ? 4 : 1) void k_
   // one copy of the collision's code for all levels
 #pragma unroll 1
   for (int lv = 0;;) {
-    collide_cell<ST, R, 2, MODEL, COLL>(f, ph, dl);
+    collide_cell<true, R, 2, MODEL, COLL>(f, ph, dl);
     if (++lv == T) break;
     if (lv > 1) __syncthreads();
 #pragma unroll
@@ -328,7 +328,7 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_cols(const Grid g, void* 
   for (int j = 0; j < nj; ++j) {
     zr = zr + 1 == nz ? 0 : zr + 1;
     R dl;
-    collide_cell<ST_F32, R, 3, MODEL, COLL>(f, ph, dl);
+    collide_cell<true, R, 3, MODEL, COLL>(f, ph, dl);
     if (j + 1 < nj) load(nf, zr);
     auto& e = xch[j & 1];
 #pragma unroll
@@ -354,7 +354,7 @@ __global__ __launch_bounds__(64 * kColWaves, 2) void k_cols(const Grid g, void* 
     }
     if (j >= 2) {
       if (inner) {
-        collide_cell<ST_F32, R, 3, MODEL, COLL>(h, ph, dl);
+        collide_cell<true, R, 3, MODEL, COLL>(h, ph, dl);
         const unsigned zo = (unsigned)zw * pl, zp = (unsigned)(zw + 1 == nz ? 0 : zw + 1) * pl,
                        zm = (unsigned)(zw == 0 ? nz - 1 : zw - 1) * pl;
         const unsigned dst[NQ] = {(zo + ro + xo) * ES, (zo + ro + xp) * ES, (zo + ro + xm) * ES, (zo + rp + xo) * ES,

@@ -110,6 +110,7 @@ __global__ __launch_bounds__(256, (MODEL == 1 && ST == ST_F32 && PAR == 0 && COL
   static_assert(!FLAT || (BODY == 0 && !FX), "flat workgroups: no body, no faces");
   constexpr bool kBB = BODY == 1 || BODY == 4;     // link-wise bounce-back (mask)
   constexpr bool kInBox = BODY == 2 || BODY == 4;  // grid over the body's box
+  constexpr bool kFix = BODY == 0 && !FX && kFixedRounding<ST, D, MODEL, SRC, FLAT>;
   __shared__ XchLds<T, K, XCH> xl;
   // BODY 2 runs over the body's box only (grid = box extent, offset by its corner);
   // BODY 3 is the plain sweep of every other cell.
@@ -357,10 +358,10 @@ __global__ __launch_bounds__(256, (MODEL == 1 && ST == ST_F32 && PAR == 0 && COL
       static_assert(D == 3 && MODEL == 0, "homogenized body: D3Q7 ideal MHD");
       R Q[K], pt;
       const bool near = HlbmTarget::near_body(bd, x, y, z);
-      collide_cell<ST, R, D, MODEL, COLL>(f, ph, dl, Q, pt, HlbmTarget{&bd, x, y, z, near, ph.s, ph.gm1});
+      collide_cell<kFix, R, D, MODEL, COLL>(f, ph, dl, Q, pt, HlbmTarget{&bd, x, y, z, near, ph.s, ph.gm1});
     } else if constexpr (INJ && MODEL == 0) {
       R Q[K], pt;
-      collide_cell<ST, R, D, MODEL, COLL>(f, ph, dl, Q, pt);
+      collide_cell<kFix, R, D, MODEL, COLL>(f, ph, dl, Q, pt);
       if (mo.x && own) {  // the moments the next network evaluation takes
         const size_t N = (size_t)g.nx * g.ny * g.nz;
         unsigned h[K];
@@ -381,14 +382,14 @@ __global__ __launch_bounds__(256, (MODEL == 1 && ST == ST_F32 && PAR == 0 && COL
       R sp[K], Q[K], pt;
 #pragma unroll
       for (int k = 0; k < K; ++k) sp[k] = sprev[(size_t)k * N + c];
-      collide_cell<ST, R, D, MODEL, COLL, NoTarget, SRC>(f, ph, dl, Q, pt, NoTarget{}, sp);
+      collide_cell<kFix, R, D, MODEL, COLL, NoTarget, SRC>(f, ph, dl, Q, pt, NoTarget{}, sp);
 #pragma unroll
       for (int k = 0; k < K; ++k) sprev[(size_t)k * N + c] = sp[k];
     } else if constexpr (SRC == 1) {
       R Q[K], pt;
-      collide_cell<ST, R, D, MODEL, COLL, NoTarget, SRC>(f, ph, dl, Q, pt);
+      collide_cell<kFix, R, D, MODEL, COLL, NoTarget, SRC>(f, ph, dl, Q, pt);
     } else {
-      collide_cell<ST, R, D, MODEL, COLL, FLAT>(f, ph, dl);
+      collide_cell<kFix, R, D, MODEL, COLL>(f, ph, dl);
     }
     if constexpr (PK) {
 #pragma unroll
@@ -486,7 +487,7 @@ __global__ __launch_bounds__(256, (MODEL == 1 && ST == ST_F32 && PAR == 0 && COL
   } else {
     static_assert(D == 3 && MODEL == 0, "body bounce-back: D3Q7 ideal MHD");
     R Q[K], pt;
-    collide_cell<ST, R, D, MODEL, COLL>(f, ph, dl, Q, pt);
+    collide_cell<kFix, R, D, MODEL, COLL>(f, ph, dl, Q, pt);
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
       const unsigned dst = (i == 0) ? co : ((i & 1) ? np[(i - 1) >> 1] : nm[(i - 1) >> 1]);
@@ -575,6 +576,7 @@ __global__ __launch_bounds__(256) void k_sweep2(const Grid g, const Phys ph, con
   using H = typename S::T;
   constexpr int NQ = 2 * D + 1;
   constexpr int K = kNVars<MODEL>;
+  constexpr bool kFix = kFixedRounding<ST, D, MODEL, 0, FLAT>;
   __shared__ XchLds<unsigned, K, true> xl;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, nw = (int)(blockDim.x >> 6);
   static_assert(!FLAT || !(BOX || FX), "flat workgroups: no body, no faces");
@@ -744,7 +746,7 @@ __global__ __launch_bounds__(256) void k_sweep2(const Grid g, const Phys ph, con
       }
     }
     R dl;
-    collide_cell<ST, R, D, MODEL, COLL, FLAT>(f, ph, dl);
+    collide_cell<kFix, R, D, MODEL, COLL>(f, ph, dl);
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
