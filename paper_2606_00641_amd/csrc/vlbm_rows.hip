@@ -17,8 +17,8 @@
 //
 // Bound by one wavefront per SIMD working through its levels (293 VGPRs for 8 variables in
 // FP32 and 4 levels; held to 256 they spill, and a step took 105 us instead of 28 on
-// 1024^2).  Per step, the in-place sweep against passes: 8 variables FP32 1024^2 61.2 ->
-// 27.5 us, 2000^2 232 -> 82 us (4 levels; 3 levels at two wavefronts per SIMD 39 and 175).
+// 1024^2).  Per step, the in-place sweep against passes: 8 variables FP32 1024^2 57.8 ->
+// 26.4 us, 1400^2 115 -> 43.3, 2000^2 240 -> 81.1 (4 levels; 3 levels at two wavefronts per SIMD 39 and 175).
 #include "vlbm_device.h"
 
 namespace vlbm {
@@ -162,9 +162,9 @@ hipError_t rows_t(const Launch& L, const Grid& g, void* out, const Phys& ph) {
 // 1.2 us a level in FP64, 0.8 in FP32), on large ones by the overlap: 512 threads complete 260
 // cells, 256 threads 100.  Neighbouring tiles go to one XCD, whose L2 then holds what they
 // share (512^2 FP32 10.3 -> 7.1 us).  Per step, the in-place sweep against passes of 4: 8
-// variables FP64 64^2 4.6 -> 2.3 us, 256^2 8.0 -> 5.0, 1024^2 124 -> 70 (k_rows 86); FP32
-// 64^2 4.3 -> 1.8, 512^2 18 -> 7.1 (k_rows 12.3); 13 variables FP64 64^2 6.6 -> 3.5, 2000^2
-// 838 -> 649, FP32 256^2 9.0 -> 4.7, 2000^2 405 -> 267 (k_rows, 2 levels, 294).
+// variables FP64 64^2 4.7 -> 2.4 us, 256^2 7.9 -> 5.1, 1024^2 116 -> 73 (k_rows 86); FP32
+// 64^2 5.5 -> 1.9, 512^2 18.0 -> 6.9 (k_rows 12.3), 800^2 37 -> 13.1; 13 variables FP64 64^2
+// 5.7 -> 3.7, 2000^2 822 -> 677, FP32 256^2 7.5 -> 5.6, 2000^2 414 -> 258 (k_rows, 2 levels, 294).
 // 5 variables in FP64 are held to 128 VGPRs, four wavefronts per SIMD, for which their LDS leaves
 // room (at 130: 2000^2 114 -> 147 us a step).
 template <int ST, int MODEL, int T, int TX, int TY, int COLL>
@@ -273,12 +273,13 @@ hipError_t tiles_t(const Launch& L, const Grid& g, void* out, const Phys& ph) {
 // which the stores of the plane before drain (120^3 110 -> 103 us a step), and the columns
 // are shared evenly among as few strips as hold them (190^3 570 -> 420 us: four strips of 48
 // columns instead of three of 62 and one of 4), in multiples of eight, whole 32-byte sectors.
-// Per step, the in-place sweep against passes, 8 variables: 64^3 23.7 -> 20.3 us, 160^3
-// 361 -> 241, 190^3 663 -> 420, 256^3 1340 -> 1204; 5 variables 90^3 38.5 -> 24.5, 210^3 566
-// -> 374; 9 variables 110^3 137 -> 117, 230^3 1378 -> 958.  A tile of any width with both
+// Per step, the in-place sweep against passes, 8 variables: 64^3 23.5 -> 18.8 us, 120^3
+// 146 -> 100, 160^3 351 -> 226, 190^3 656 -> 402, 256^3 1351 -> 1217; 5 variables 90^3 38.5 ->
+// 23.7, 210^3 576 -> 367; 9 variables 110^3 150 -> 112, 230^3 1373 -> 940 to 1070 (lattices over
+// about 4 GB vary by a tenth with where their memory lies).  A tile of any width with both
 // exchanges through LDS, and strips that run on over the rows' ends, fill the lanes better
 // but need per-lane row addresses and spill: 190^3 474 and 698 us, 240^3 1010 and 1263
-// against 873.  Twelve wavefronts in 168 VGPRs spill more (160^3 415 us).
+// against 873 (strips as they are).  Twelve wavefronts in 168 VGPRs spill more (160^3 415 us).
 constexpr int kColWaves = 8, kColRows = kColWaves - 2, kColV = 62;
 template <int MODEL, int COLL>
 __global__ __launch_bounds__(64 * kColWaves, 2) void k_cols(const Grid g, void* const out, const Phys ph, int V, int planes) {
